@@ -1,6 +1,6 @@
-// Dense contractions of the training step: bf16 MFMA GEMM (gfx950
-// v_mfma_f32_32x32x16_bf16, fp32 accumulate) and an fp32 FMA GEMM for the
-// full-precision mode, both with the fused epilogues the step needs
+// Dense contractions of the training step: register-staged bf16 MFMA GEMM
+// (gfx950 v_mfma_f32_32x32x16_bf16, fp32 accumulate) and the dispatch over all
+// GEMM kernels, with the fused epilogues the step needs
 // (bias, bias+GeLU with saved pre-activation, GeLU-gradient multiply, residual
 // add, scale, fp32 output).  Pattern-based "GEMM + elementwise epilogue"
 // fusion in the sense of the paper's Section 3.2.2.
@@ -207,54 +207,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_group_kernel(GemmGro
   staged_tile<BM, BN, WGM, WGN, A_KMAJOR, B_KMAJOR, TC>(grp.p[p], (lt / tn) * BM, (lt % tn) * BN, 0, lds_a, lds_b);
 }
 
-// -------------------------------------------------------------- fp32 FMA --
-// Plain LDS-tiled FMA kernel for the full-precision mode (small validation
-// shapes): 64x64 tile, 16x16 threads, 4x4 outputs each, any strides.
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmDev g, long sa_i, long sa_k, long sb_k, long sb_j) {
-  constexpr int T = 64, KT = 16;
-  __shared__ float As[KT][T + 1];
-  __shared__ float Bs[KT][T + 1];
-  const int z = blockIdx.z;
-  const int zb = z / g.nz_inner, zi = z % g.nz_inner;
-  const float* __restrict__ A = (const float*)g.a + zb * g.sa0 + zi * g.sa1;
-  const float* __restrict__ B = (const float*)g.b + zb * g.sb0 + zi * g.sb1;
-  float* __restrict__ C = (float*)g.c + zb * g.sc0 + zi * g.sc1;
-  float* __restrict__ AUX = g.aux ? (float*)g.aux + zb * g.sc0 + zi * g.sc1 : nullptr;
-  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < g.K; k0 += KT) {
-    for (int e = threadIdx.x; e < T * KT; e += 256) {
-      const int r = e / KT, k = e % KT;     // k fastest: good for k-major operands
-      const int i = m0 + r, j = n0 + r, kk = k0 + k;
-      As[k][r] = (i < g.M && kk < g.K) ? A[i * sa_i + kk * sa_k] : 0.f;
-      Bs[k][r] = (j < g.N && kk < g.K) ? B[kk * sb_k + j * sb_j] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < KT; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = As[k][ty * 4 + u];
-        b[u] = Bs[k][tx * 4 + u];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) acc[u][w] = fmaf(a[u], b[w], acc[u][w]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int i = m0 + ty * 4 + u, j = n0 + tx * 4 + w;
-      if (i < g.M && j < g.N) epilogue_store<float, float>(g, C, AUX, i, j, acc[u][w]);
-    }
-}
-
 // ---------------------------------------------------------------- launch --
 template <int BM, int BN, int WGM, int WGN, bool AK, bool BKM>
 static void launch_bf16_tile(const GemmDev& d, int out_f32, int batch, hipStream_t st) {
@@ -388,12 +340,12 @@ raf_status launch_gemm_group_wgrad(int precision, const GemmArgs* gs, int count,
                                    int nside, const ReduceJob* reds, int nred, bool* side_taken, int* nonfinite) {
   if (side_taken) *side_taken = false;
   if (count <= 0 || count > GEMM_GROUP_MAX || !gs) return RAF_EINVAL;
-  bool groupable = precision == RAF_BF16_AMP;
+  bool groupable = true;
   for (int i = 0; i < count; ++i) {
     raf_status rc = check_gemm_args(gs[i]);
     if (rc != RAF_OK) return rc;
     if (gs[i].a_kmajor || gs[i].b_kmajor || !gs[i].out_f32 || gs[i].batch != 1 || gs[i].epilogue != EPI_NONE ||
-        gs[i].M < 128 || gs[i].N < 128)
+        (precision == RAF_BF16_AMP && (gs[i].M < 128 || gs[i].N < 128)))
       groupable = false;
   }
   if (!groupable) {
@@ -403,9 +355,10 @@ raf_status launch_gemm_group_wgrad(int precision, const GemmArgs* gs, int count,
     }
     return RAF_OK;
   }
+  GemmDev ds[GEMM_GROUP_MAX];
+  for (int i = 0; i < count; ++i) ds[i] = to_dev(gs[i]);
+  if (precision == RAF_F32) return launch_gemm_f32_group(ds, count, st) ? check_launch() : RAF_EHIP;
   if (precision == RAF_BF16_AMP) {
-    GemmDev ds[GEMM_GROUP_MAX];
-    for (int i = 0; i < count; ++i) ds[i] = to_dev(gs[i]);
     // column sums of up to two bf16 matrices with a common row count can ride along on idle CUs
     ColsumSide sd{};
     sd.nonfinite = nonfinite;
@@ -459,10 +412,7 @@ raf_status launch_gemm(int precision, const GemmArgs& g, hipStream_t st) {
   if (rc != RAF_OK) return rc;
   const GemmDev d = to_dev(g);
   if (precision == RAF_F32) {
-    dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, g.batch);
-    const long sa_i = g.a_kmajor ? g.lda : 1, sa_k = g.a_kmajor ? 1 : g.lda;
-    const long sb_k = g.b_kmajor ? 1 : g.ldb, sb_j = g.b_kmajor ? g.ldb : 1;
-    hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, st, d, sa_i, sa_k, sb_k, sb_j);
+    if (!launch_gemm_f32(d, g.a_kmajor, g.b_kmajor, g.batch, st)) return RAF_EHIP;
   } else if (precision == RAF_BF16_AMP) {
     if (!g.a_kmajor && !g.b_kmajor && g.out_f32 && g.batch == 1 && g.epilogue == EPI_NONE &&
         launch_gemm_group_spec(&d, 1, st))

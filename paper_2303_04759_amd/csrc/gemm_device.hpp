@@ -20,49 +20,6 @@ struct GemmDev {
   long sa0, sa1, sb0, sb1, sc0, sc1;
 };
 
-template <typename TC, typename TAUX>
-__device__ __forceinline__ float epilogue_value(const GemmDev& g, TAUX* __restrict__ aux, int i, int j, float acc) {
-  float v = acc * g.alpha;
-  switch (g.epilogue) {
-    case EPI_BIAS:
-      v += g.bias[j];
-      break;
-    case EPI_BIAS_GELU: {
-      v += g.bias[j];
-      aux[(long)i * g.ldaux + j] = (TAUX)v;
-      // GeLU is evaluated on the value the backward pass will read back
-      v = gelu_f((float)(TAUX)v, g.gelu_tanh);
-      break;
-    }
-    case EPI_MUL_GELU_GRAD:
-      v *= gelu_grad_f((float)aux[(long)i * g.ldaux + j], g.gelu_tanh);
-      break;
-    case EPI_ADD_RES:
-      v += (float)aux[(long)i * g.ldaux + j];
-      break;
-    case EPI_BIAS_GELU_DERIV: {
-      v += g.bias[j];
-      float y, dy;
-      gelu_and_grad_f(v, g.gelu_tanh, y, dy);
-      aux[(long)i * g.ldaux + j] = (TAUX)dy;
-      v = y;
-      break;
-    }
-    case EPI_MUL_AUX:
-      v *= (float)aux[(long)i * g.ldaux + j];
-      break;
-    default:
-      break;
-  }
-  return v;
-}
-
-template <typename TC, typename TAUX>
-__device__ __forceinline__ void epilogue_store(const GemmDev& g, TC* __restrict__ c, TAUX* __restrict__ aux, int i,
-                                               int j, float acc) {
-  c[(long)i * g.ldc + j] = (TC)epilogue_value<TC, TAUX>(g, aux, i, j, acc);
-}
-
 // four consecutive columns j..j+3 of row i (j a multiple of 4; all pointers and
 // leading dimensions keep 8-byte alignment of such groups)
 __device__ __forceinline__ void load4(const bf16_t* p, float (&o)[4]) {
@@ -346,6 +303,25 @@ __device__ __forceinline__ void epilogue_tile32_staged(const GemmDev& g, float* 
     }
 }
 
+// s_waitcnt on the vector-memory counter only (expcnt / lgkmcnt left at max)
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+// s_waitcnt vmcnt(n) for a wave-uniform run-time n (conservative above 24)
+__device__ __forceinline__ void wait_vmcnt_dyn(int n) {
+  switch (n) {
+#define RAF_VMCNT_CASE(N) case N: wait_vmcnt<N>(); break;
+    RAF_VMCNT_CASE(1) RAF_VMCNT_CASE(2) RAF_VMCNT_CASE(3) RAF_VMCNT_CASE(4) RAF_VMCNT_CASE(5) RAF_VMCNT_CASE(6)
+    RAF_VMCNT_CASE(7) RAF_VMCNT_CASE(8) RAF_VMCNT_CASE(9) RAF_VMCNT_CASE(10) RAF_VMCNT_CASE(11) RAF_VMCNT_CASE(12)
+    RAF_VMCNT_CASE(13) RAF_VMCNT_CASE(14) RAF_VMCNT_CASE(15) RAF_VMCNT_CASE(16) RAF_VMCNT_CASE(17) RAF_VMCNT_CASE(18)
+    RAF_VMCNT_CASE(19) RAF_VMCNT_CASE(20) RAF_VMCNT_CASE(21) RAF_VMCNT_CASE(22) RAF_VMCNT_CASE(23) RAF_VMCNT_CASE(24)
+#undef RAF_VMCNT_CASE
+    default: wait_vmcnt<0>(); break;
+  }
+}
+
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x8_t __attribute__((ext_vector_type(8)));
 
@@ -392,5 +368,10 @@ bool launch_gemm_group_spec(const GemmDev* ds, int count, hipStream_t st, const 
 // the problem does not meet its requirements (K % 64, tile fit) and the
 // caller must use the staged kernel instead.
 bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32, int batch, hipStream_t st);
+
+// Full-precision products on the matrix cores (gemm_f32.hip), one problem (batched or not) of any layout, or up to
+// GEMM_GROUP_MAX of the weight-gradient layout in one launch.  False: the kernel could not be set up (raf_last_hip_error).
+bool launch_gemm_f32(const GemmDev& d, int a_kmajor, int b_kmajor, int batch, hipStream_t st);
+bool launch_gemm_f32_group(const GemmDev* ds, int count, hipStream_t st);
 
 }  // namespace raf

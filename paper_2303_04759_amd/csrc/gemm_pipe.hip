@@ -87,25 +87,6 @@ __device__ __forceinline__ bf16x8_t pipe_fragment(const char* lds_tile, int row,
   }
 }
 
-// s_waitcnt on the vector-memory counter only (expcnt / lgkmcnt left at max)
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
-// s_waitcnt vmcnt(n) for a wave-uniform run-time n (conservative above 24)
-__device__ __forceinline__ void wait_vmcnt_dyn(int n) {
-  switch (n) {
-#define RAF_VMCNT_CASE(N) case N: wait_vmcnt<N>(); break;
-    RAF_VMCNT_CASE(1) RAF_VMCNT_CASE(2) RAF_VMCNT_CASE(3) RAF_VMCNT_CASE(4) RAF_VMCNT_CASE(5) RAF_VMCNT_CASE(6)
-    RAF_VMCNT_CASE(7) RAF_VMCNT_CASE(8) RAF_VMCNT_CASE(9) RAF_VMCNT_CASE(10) RAF_VMCNT_CASE(11) RAF_VMCNT_CASE(12)
-    RAF_VMCNT_CASE(13) RAF_VMCNT_CASE(14) RAF_VMCNT_CASE(15) RAF_VMCNT_CASE(16) RAF_VMCNT_CASE(17) RAF_VMCNT_CASE(18)
-    RAF_VMCNT_CASE(19) RAF_VMCNT_CASE(20) RAF_VMCNT_CASE(21) RAF_VMCNT_CASE(22) RAF_VMCNT_CASE(23) RAF_VMCNT_CASE(24)
-#undef RAF_VMCNT_CASE
-    default: wait_vmcnt<0>(); break;
-  }
-}
-
 template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, typename TC, int NS>
 __device__ __forceinline__ void pipe_body(const GemmDev& g, int tiles_m, int tiles_n, int remap, int z) {
   constexpr int NW = WGM * WGN;

@@ -184,6 +184,26 @@ def test_gemm_epilogues_and_f32_out(precision):
     assert rel_fro(host(cf), Y.astype(np.float64).T @ X.astype(np.float64)) <= 1e-5
 
 
+# Full-precision products at sizes where the tile choice (by rounds over 256 CUs) takes each of its tiles, with ragged
+# last rows and columns and contractions that end inside a ring stage: 64x192, 64x144, 64x96, 64x64, 64x48, 32x32.
+# The bound is float32 accumulation in any order: |error| <= K 2^-24 sum |a||b| per element, and per norm far less.
+@pytest.mark.parametrize("ak,bk", [(1, 1), (1, 0), (0, 0), (0, 1)])
+@pytest.mark.parametrize("M,N,K", [(992, 3040, 96), (992, 2272, 160), (992, 1504, 64), (992, 992, 32), (992, 736, 224),
+                                   (32, 64, 288), (64, 32, 32)])
+def test_gemm_f32_tiles(M, N, K, ak, bk):
+    announce("gemm-f32-tiles", M, N, K, ak, bk)
+    rng = np.random.default_rng(M + N + K + 2 * ak + bk)
+    A, Bm = rnd(rng, (M, K), 0), rnd(rng, (K, N), 0)
+    a_dev, b_dev = to_dev(A if ak else A.T, torch.float32), to_dev(Bm.T if bk else Bm, torch.float32)
+    c = torch.full((M, N), float("nan"), device="cuda")
+    raf.raf_op_gemm(0, M, N, K, a_dev, a_dev.shape[1], ak, b_dev, b_dev.shape[1], bk, c, N)
+    torch.cuda.synchronize()
+    A64, B64 = A.astype(np.float64), Bm.astype(np.float64)
+    err = np.abs(host(c) - A64 @ B64)
+    assert (err <= K * 2.0 ** -24 * (np.abs(A64) @ np.abs(B64))).all(), float(err.max())
+    assert rel_fro(host(c), A64 @ B64) <= 1e-6
+
+
 # ---------------------------------------------------------------- softmax --
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("B,S,causal,p", [(2, 32, 0, 0.0), (3, 96, 1, 0.1), (2, 128, 0, 0.1), (1, 512, 0, 0.1),
