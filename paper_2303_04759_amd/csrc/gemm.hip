@@ -185,28 +185,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(GemmDev g, in
                                                           lds_b);
 }
 
-// Several independent problems of one layout in a single launch (the four
-// weight-gradient GEMMs of a layer: each alone has too few tiles to fill the
-// chip).  tile_start[p] is the first linear tile of problem p.
-
-template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, typename TC>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_group_kernel(GemmGroupDev grp) {
-  constexpr int NTHREADS = 64 * WGM * WGN;
-  __shared__ __attribute__((aligned(16))) bf16_t lds_a[TileLds<BM, A_KMAJOR, NTHREADS>::ELEMS];
-  __shared__ __attribute__((aligned(16))) bf16_t lds_b[TileLds<BN, B_KMAJOR, NTHREADS>::ELEMS];
-  const int ntile = grp.tile_start[grp.count];
-  const int t = xcd_tile(blockIdx.x, ntile);
-  if (t >= ntile) return;
-  int p = 0;
-#pragma unroll
-  for (int q = 1; q < GEMM_GROUP_MAX; ++q)
-    if (q < grp.count && t >= grp.tile_start[q]) p = q;
-  const int lt = t - grp.tile_start[p];
-  const int tn = grp.tiles_n[p];
-  // the problem descriptor is selected with wave-uniform scalar loads
-  staged_tile<BM, BN, WGM, WGN, A_KMAJOR, B_KMAJOR, TC>(grp.p[p], (lt / tn) * BM, (lt % tn) * BN, 0, lds_a, lds_b);
-}
-
 // ---------------------------------------------------------------- launch --
 template <int BM, int BN, int WGM, int WGN, bool AK, bool BKM>
 static void launch_bf16_tile(const GemmDev& d, int out_f32, int batch, hipStream_t st) {
@@ -344,8 +322,7 @@ raf_status launch_gemm_group_wgrad(int precision, const GemmArgs* gs, int count,
   for (int i = 0; i < count; ++i) {
     raf_status rc = check_gemm_args(gs[i]);
     if (rc != RAF_OK) return rc;
-    if (gs[i].a_kmajor || gs[i].b_kmajor || !gs[i].out_f32 || gs[i].batch != 1 || gs[i].epilogue != EPI_NONE ||
-        (precision == RAF_BF16_AMP && (gs[i].M < 128 || gs[i].N < 128)))
+    if (gs[i].a_kmajor || gs[i].b_kmajor || !gs[i].out_f32 || gs[i].batch != 1 || gs[i].epilogue != EPI_NONE)
       groupable = false;
   }
   if (!groupable) {
@@ -358,53 +335,35 @@ raf_status launch_gemm_group_wgrad(int precision, const GemmArgs* gs, int count,
   GemmDev ds[GEMM_GROUP_MAX];
   for (int i = 0; i < count; ++i) ds[i] = to_dev(gs[i]);
   if (precision == RAF_F32) return launch_gemm_f32_group(ds, count, st) ? check_launch() : RAF_EHIP;
-  if (precision == RAF_BF16_AMP) {
-    // column sums of up to two bf16 matrices with a common row count can ride along on idle CUs
-    ColsumSide sd{};
-    sd.nonfinite = nonfinite;
-    if (side && nside >= 1 && nside <= 2) {
-      bool ok = true;
-      for (int i = 0; i < nside; ++i)
-        ok = ok && side[i].precision == RAF_BF16_AMP && side[i].x && side[i].out && side[i].cols > 0 &&
-             side[i].cols % 8 == 0 && side[i].ld % 8 == 0 && side[i].rows == side[0].rows && aligned16(side[i].x) &&
-             (side[i].out_cols == 0 || side[i].out_cols == side[i].cols);
-      if (ok) {
-        sd.count = nside;
-        sd.rows = side[0].rows;
-        for (int i = 0; i < nside; ++i) {
-          sd.x[i] = (const bf16_t*)side[i].x;
-          sd.out[i] = side[i].out;
-          sd.ld[i] = side[i].ld;
-          sd.cols[i] = side[i].cols;
-        }
-        if (nside == 1) { sd.x[1] = sd.x[0]; sd.out[1] = sd.out[0]; sd.ld[1] = sd.ld[0]; sd.cols[1] = 0; }
-        sd.nred = 0;
-        if (reds && nred > 0 && nred <= 3) {
-          for (int i = 0; i < nred; ++i) sd.red[i] = reds[i];
-          sd.nred = nred;
-        } else if (nred > 3) {
-          sd.count = 0;   // more second stages than the side workers take: the caller launches everything itself
-        }
+  // column sums of up to two bf16 matrices with a common row count can ride along on idle CUs
+  ColsumSide sd{};
+  sd.nonfinite = nonfinite;
+  if (side && nside >= 1 && nside <= 2) {
+    bool ok = true;
+    for (int i = 0; i < nside; ++i)
+      ok = ok && side[i].precision == RAF_BF16_AMP && side[i].x && side[i].out && side[i].cols > 0 &&
+           side[i].cols % 8 == 0 && side[i].ld % 8 == 0 && side[i].rows == side[0].rows && aligned16(side[i].x) &&
+           (side[i].out_cols == 0 || side[i].out_cols == side[i].cols);
+    if (ok) {
+      sd.count = nside;
+      sd.rows = side[0].rows;
+      for (int i = 0; i < nside; ++i) {
+        sd.x[i] = (const bf16_t*)side[i].x;
+        sd.out[i] = side[i].out;
+        sd.ld[i] = side[i].ld;
+        sd.cols[i] = side[i].cols;
+      }
+      if (nside == 1) { sd.x[1] = sd.x[0]; sd.out[1] = sd.out[0]; sd.ld[1] = sd.ld[0]; sd.cols[1] = 0; }
+      sd.nred = 0;
+      if (reds && nred > 0 && nred <= 3) {
+        for (int i = 0; i < nred; ++i) sd.red[i] = reds[i];
+        sd.nred = nred;
+      } else if (nred > 3) {
+        sd.count = 0;   // more second stages than the side workers take: the caller launches everything itself
       }
     }
-    if (launch_gemm_group_spec(ds, count, st, sd.count ? &sd : nullptr, side_taken)) return check_launch();
   }
-  GemmGroupDev grp;
-  grp.count = count;
-  int tiles = 0;
-  for (int i = 0; i < count; ++i) {
-    grp.p[i] = to_dev(gs[i]);
-    grp.tile_start[i] = tiles;
-    grp.tiles_n[i] = (gs[i].N + 127) / 128;
-    tiles += ((gs[i].M + 127) / 128) * grp.tiles_n[i];
-  }
-  for (int i = count; i <= GEMM_GROUP_MAX; ++i) grp.tile_start[i] = tiles;
-  for (int i = 0; i < GEMM_GROUP_MAX; ++i) grp.tiles_m_first[i] = 0;
-  for (int i = count; i < GEMM_GROUP_MAX; ++i) { grp.p[i] = grp.p[0]; grp.tiles_n[i] = 1; }
-  dim3 grid(((tiles + 7) / 8) * 8);
-  // 8 wavefronts per workgroup measured faster than 4 even with ~1.7 workgroups per CU
-  hipLaunchKernelGGL((gemm_bf16_group_kernel<128, 128, 2, 4, false, false, float>), grid, dim3(512), 0, st, grp);
-  return check_launch();
+  return launch_gemm_group_spec(ds, count, st, sd.count ? &sd : nullptr, side_taken) ? check_launch() : RAF_EHIP;
 }
 
 raf_status launch_gemm(int precision, const GemmArgs& g, hipStream_t st) {
@@ -414,7 +373,7 @@ raf_status launch_gemm(int precision, const GemmArgs& g, hipStream_t st) {
   if (precision == RAF_F32) {
     if (!launch_gemm_f32(d, g.a_kmajor, g.b_kmajor, g.batch, st)) return RAF_EHIP;
   } else if (precision == RAF_BF16_AMP) {
-    if (!g.a_kmajor && !g.b_kmajor && g.out_f32 && g.batch == 1 && g.epilogue == EPI_NONE &&
+    if (!g.a_kmajor && !g.b_kmajor && g.out_f32 && g.batch == 1 && g.epilogue == EPI_NONE && g.M >= 128 && g.N >= 128 &&
         launch_gemm_group_spec(&d, 1, st))
       return check_launch();
     if (launch_gemm_pipe(d, g.a_kmajor, g.b_kmajor, g.out_f32, g.batch, st)) return check_launch();

@@ -270,37 +270,30 @@ __device__ __forceinline__ void epilogue_tile16_staged(const GemmDev& g, bf16_t*
   });
 }
 
-// Float outputs of the 32x32 layout without elementwise epilogue (weight gradients), one 32x32 block per trip
-// through a wave-private LDS buffer of epilogue_stage32_bytes: a direct store instruction writes 32-byte pieces of
-// 32 rows, the staged one whole 128-byte rows.
-constexpr int epilogue_stage32_bytes = 32 * (128 + 16);
-__device__ __forceinline__ bool epilogue_can_stage32(const GemmDev& g) {
-  return g.epilogue == EPI_NONE && ((g.ldc | (long)g.N) & 3) == 0 && ((unsigned long long)g.c & 15) == 0;
+// Float outputs of the 16x16 layout without elementwise epilogue (weight gradients), one row of blocks per trip
+// through a wave-private LDS buffer of epilogue_stage_f32_bytes: a direct store instruction writes 64-byte pieces of
+// 16 rows, the staged one runs along whole rows of the wave tile.
+template <int NB>
+constexpr int epilogue_stage_f32_bytes() {
+  return 16 * (64 * NB + 16);
 }
-template <int TM, int TN>
-__device__ __forceinline__ void epilogue_tile32_staged(const GemmDev& g, float* __restrict__ C,
-                                                       f32x16_t (&acc)[TM][TN], int row0, int col0, char* stg) {
-  constexpr int P = 128 + 16;
-  const int lane = threadIdx.x & 63;
-  const int wr = lane & 31, wh = lane >> 5;     // accumulator layout: row, which 4 of every 8 columns
-  const int rr = lane >> 3, rc = lane & 7;      // copy-out: row within 8, 16-byte piece of the row
+template <int MB, int NB>
+__device__ __forceinline__ void epilogue_tile16_f32(const GemmDev& g, float* __restrict__ C, f32x4_t (&acc)[MB][NB],
+                                                    int row0, int col0, char* stg) {
+  constexpr int P = 64 * NB + 16, CPR = 4 * NB;   // row pitch in bytes, 16-byte pieces per row
+  const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < MB; ++i) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
+    for (int j = 0; j < NB; ++j) *reinterpret_cast<f32x4_t*>(stg + lr * P + j * 64 + lg * 16) = acc[i][j] * g.alpha;
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<float4*>(stg + wr * P + q * 32 + wh * 16) =
-            make_float4(acc[i][j][4 * q] * g.alpha, acc[i][j][4 * q + 1] * g.alpha, acc[i][j][4 * q + 2] * g.alpha,
-                        acc[i][j][4 * q + 3] * g.alpha);
-#pragma unroll
-      for (int it = 0; it < 4; ++it) {
-        const int r = it * 8 + rr;
-        const int row = row0 + i * 32 + r, col = col0 + j * 32 + rc * 4;
-        if (row < g.M && col < g.N)
-          *reinterpret_cast<float4*>(C + (long)row * g.ldc + col) = *reinterpret_cast<const float4*>(stg + r * P + rc * 16);
-      }
+    for (int it = 0; it < 16 * CPR / 64; ++it) {
+      const int q = it * 64 + lane, r = q / CPR, c = q % CPR;
+      const int row = row0 + i * 16 + r, col = col0 + c * 4;
+      if (row < g.M && col < g.N)   // N is a multiple of 8: a piece is inside or outside as a whole
+        *reinterpret_cast<f32x4_t*>(C + (long)row * g.ldc + col) = *reinterpret_cast<const f32x4_t*>(stg + r * P + c * 16);
     }
+  }
 }
 
 // s_waitcnt on the vector-memory counter only (expcnt / lgkmcnt left at max)
@@ -358,7 +351,7 @@ struct ColsumSide {
 
 // Weight-gradient group (both operands MN-major, float output) on the
 // producer/consumer direct-to-LDS kernel (gemm_pipe.hip); false when a problem
-// does not fit it (K % 64, sizes below one tile).  side: optional column sums; *side_taken tells whether the launch
+// does not fit it (K % 32, M or N not a multiple of 8) or the kernel could not be set up.  side: optional column sums; *side_taken tells whether the launch
 // computed them (it does when enough CUs are left without a tile), otherwise the caller has to.
 // side->nonfinite is honoured only when the side work is taken (*side_taken).
 bool launch_gemm_group_spec(const GemmDev* ds, int count, hipStream_t st, const ColsumSide* side = nullptr,

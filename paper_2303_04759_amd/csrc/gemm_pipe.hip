@@ -222,16 +222,62 @@ static bool launch_pipe_inst(const GemmDev& d, int batch, hipStream_t st) {
 // barrier per k-step keeps both sides in step: after barrier `it` the consumers
 // work on stage it while the producers refill the stage that was just freed
 // and then wait until stage it+1 has landed.
+//
+// The MFMA is the 16x16x32 one: while 32x32x16 MFMAs (twice as long per
+// instruction) of one wave run back to back, its SIMD issues no memory or LDS
+// instruction of any other wave, so that loads and MFMAs add up; the shorter
+// ones overlap with both (probe with computing and loading waves: 239 000 clocks
+// for the MFMAs, 141 000 for the loads, together 329 000 to 372 000 with 32x32x16
+// and 240 000 with 16x16x32).  The group of a 768-wide layer over 4096 rows went from 76
+// to 62 us, 1024-wide 126 to 108 us, 2048-wide 406 to 371 us, bit-identical.  What is
+// left: per 64 contraction values a 256x128 tile needs 1024 clocks of MFMA, about
+// 900 of LDS (131 KiB read transposed at 210 bytes/clock, 48 written) and 850 of
+// direct loads (48 KiB at 57), and takes 1900.  Fragments read across the barrier,
+// two wave groups alternating between reading and computing, 128x64 wave
+// tiles and 256x256 tiles all measured slower (66 to 70 us, 64, 141).
+//
+// LDS layout of a [64][ROWS] tile: 16-byte chunk cc of k-row k sits at chunk
+// cc ^ wg_swz(k), which spreads the eight k-rows x 32 bytes of half a fragment
+// read over all banks.
+__device__ __forceinline__ int wg_swz(int k) { return ((k & 3) | (((k >> 3) & 1) << 2)) << 1; }
+
+// per-lane source of KiB chunk q of a [64][ROWS] tile for k-step 0
+template <int ROWS>
+__device__ __forceinline__ const bf16_t* wg_src(const bf16_t* base, long ld, int col0, int ncols, int q) {
+  constexpr int CPR = ROWS / 8;
+  static_assert(CPR >= 16, "the swizzle permutes 16 chunks");
+  const int n = q * 64 + (threadIdx.x & 63), k = n / CPR;
+  int col = col0 + ((n % CPR) ^ wg_swz(k)) * 8;
+  col = col < ncols ? col : ncols - 8;
+  return base + (long)k * ld + col;
+}
+
+// operand fragment of 16 tile columns at col0: lane l holds column l & 15, k values 32*kk + 8*(l >> 4) .. +7
+template <int ROWS>
+__device__ __forceinline__ bf16x8_t wg_fragment(const char* tile, int col0, int kk) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, s = lane & 15;
+  const int k = kk * 32 + 8 * g + (s >> 2);
+  const int col = col0 + (s & 3) * 4;
+  const char* p = tile + k * (ROWS * 2) + (((col >> 3) ^ wg_swz(k)) << 4) + (col & 7) * 2;
+  typedef s16x4_t __attribute__((address_space(3))) * lds_v4_ptr;
+  const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4_ptr)(p));
+  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4_ptr)(p + 4 * ROWS * 2));   // k + 4: same swizzle
+  return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // Side work of the grouped launch: worker w of nworkers takes a contiguous range of the 8-column vectors of the
 // (concatenated) column space; its threads are dealt to (vector, row group), every row group sums its rows in
 // registers, and the row groups are added in a fixed order through LDS, so the sums are reproducible.
+constexpr int SIDE_MAX_SLICES = 64;
 __device__ __forceinline__ void colsum_side_worker(const ColsumSide& sd, int w, int nworkers, char* lds) {
   const int nvec0 = sd.cols[0] / 8, total = nvec0 + sd.cols[1] / 8;
   const int per = (total + nworkers - 1) / nworkers;
   const int v0 = w * per;
   const int nv = total - v0 < per ? total - v0 : per;
   if (per > (int)blockDim.x) return;               // uniform over the launch; the host never asks for it
-  const int ngroups = (int)blockDim.x / per;
+  // few enough row groups that adding them up at the end stays short (1024 of them, one vector per worker, took 20 us)
+  int ngroups = (int)blockDim.x / per;
+  ngroups = ngroups < SIDE_MAX_SLICES ? ngroups : SIDE_MAX_SLICES;
   const int vec = threadIdx.x % per, rg = threadIdx.x / per;
   const bool active = rg < ngroups && vec < nv;     // nv <= 0: a worker beyond the last vector idles through the barrier
   const int uv = v0 + vec;
@@ -284,7 +330,8 @@ __device__ __forceinline__ void reduce_side_worker(const ReduceJob& job, int w, 
   const int nc = job.width_out - c0 < chunk ? job.width_out - c0 : chunk;
   float* red = reinterpret_cast<float*>(lds);   // [nslices][chunk]
   const bool fits = chunk <= (int)blockDim.x;
-  const int nslices = fits ? (int)blockDim.x / chunk : 1;
+  int nslices = fits ? (int)blockDim.x / chunk : 1;
+  nslices = nslices < SIDE_MAX_SLICES ? nslices : SIDE_MAX_SLICES;
   const int cl = fits ? threadIdx.x % chunk : 0, slice = fits ? threadIdx.x / chunk : nslices;
   const long width = (long)job.nout * job.ncols;   // stride between partial rows
   __syncthreads();                                 // the previous user of the LDS buffer is done
@@ -321,18 +368,17 @@ __device__ __forceinline__ void reduce_side_worker(const ReduceJob& job, int w, 
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, typename TC, int NS, int NP>
+template <int BM, int BN, int WGM, int WGN, int NS, int NP>
 __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_bf16_spec_kernel(GemmGroupDev grp, ColsumSide side,
                                                                                int tile_blocks) {
   constexpr int NC = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
-  constexpr int TM = WM / 32, TN = WN / 32;
-  static_assert(TM >= 1 && TN >= 1, "wave tile below one MFMA block");
+  constexpr int MB = WM / 16, NB = WN / 16;
   static_assert(NS >= 3, "the producers need a stage to fill while one is read and one is in flight");
-  typedef PipeTile<BM, A_KMAJOR, NP> PA;
-  typedef PipeTile<BN, B_KMAJOR, NP> PB;
-  constexpr int STAGE_BYTES = PA::BYTES + PB::BYTES;
-  constexpr int LPS = PA::LOADS + PB::LOADS;          // loads per producer wave per stage
+  constexpr int ACH = BM / 8, BCH = BN / 8;            // KiB per operand tile
+  constexpr int STAGE_BYTES = (ACH + BCH) * 1024;
+  static_assert(ACH % NP == 0 && BCH % NP == 0 && NP % 2 == 0, "loads split evenly; half of the producers load half the k-rows");
+  constexpr int LA = ACH / NP, LB = BCH / NP, LPS = LA + LB;   // loads per producer wave per stage
   extern __shared__ __attribute__((aligned(1024))) char lds[];
 
   if ((int)blockIdx.x >= tile_blocks) {   // a workgroup without a tile: column sums on a CU that the tiles leave idle
@@ -361,35 +407,49 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_bf16_spec_kernel(G
     }
   const int m0 = (tmf ? lt % tmf : lt / tn) * BM, n0 = (tmf ? lt / tmf : lt % tn) * BN;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nk = g.K / PBK;
+  // a contraction that ends in the middle of a k-step: its second half is neither loaded nor used
+  const int nk = (g.K + PBK - 1) / PBK;
+  const bool half_last = g.K % PBK != 0;
 
   if (wave >= NC) {
     // ------------------------------------------------------------ producer
     const int pw = wave - NC;
-    const bf16_t* srca[PA::LOADS];
-    const bf16_t* srcb[PB::LOADS];
-    pipe_src_init<BM, A_KMAJOR, NP>((const bf16_t*)g.a, g.lda, m0, g.M, srca, pw);
-    pipe_src_init<BN, B_KMAJOR, NP>((const bf16_t*)g.b, g.ldb, n0, g.N, srcb, pw);
-    const long stepa = A_KMAJOR ? PBK : (long)PBK * g.lda;
-    const long stepb = B_KMAJOR ? PBK : (long)PBK * g.ldb;
+    const bf16_t* srca[LA];
+    const bf16_t* srcb[LB];
+#pragma unroll
+    for (int i = 0; i < LA; ++i) srca[i] = wg_src<BM>((const bf16_t*)g.a, g.lda, m0, g.M, pw * LA + i);
+#pragma unroll
+    for (int i = 0; i < LB; ++i) srcb[i] = wg_src<BN>((const bf16_t*)g.b, g.ldb, n0, g.N, pw * LB + i);
+    const long stepa = (long)PBK * g.lda, stepb = (long)PBK * g.ldb;
+    // chunks are dealt in order, so producers 0 .. NP/2-1 load k-rows 0 .. 31 of both tiles
+    const bool in_last = !half_last || pw < NP / 2;
+    auto issue = [&](int it, int slot) {
+      if (it == nk - 1 && !in_last) return;
+      char* base = lds + slot * STAGE_BYTES;
+#pragma unroll
+      for (int i = 0; i < LA; ++i)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srca[i] + it * stepa),
+                                         (lds_void_ptr)(base + (pw * LA + i) * 1024), 16, 0, 0);
+#pragma unroll
+      for (int i = 0; i < LB; ++i)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcb[i] + it * stepb),
+                                         (lds_void_ptr)(base + (ACH + pw * LB + i) * 1024), 16, 0, 0);
+    };
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
-      if (s < nk) {
-        pipe_issue<BM, A_KMAJOR, NP>(srca, s * stepa, lds + s * STAGE_BYTES, pw);
-        pipe_issue<BN, B_KMAJOR, NP>(srcb, s * stepb, lds + s * STAGE_BYTES + PA::BYTES, pw);
-      }
+      if (s < nk) issue(s, s);
     int stage = 0;
     for (int it = 0; it < nk; ++it) {
       // k-steps it+1 .. it+NS-2 may stay in flight; k-step `it` must have landed
-      const int ahead = nk - 1 - it < NS - 2 ? nk - 1 - it : NS - 2;
+      int ahead = nk - 1 - it < NS - 2 ? nk - 1 - it : NS - 2;
+      if (it + ahead == nk - 1 && !in_last) ahead = ahead > 0 ? ahead - 1 : 0;   // the last stage has no load of this wave
       wait_vmcnt_dyn(ahead * LPS);
       __builtin_amdgcn_s_barrier();   // stage `it` handed to the consumers; stage it-1 is free
       const int nxt = it + NS - 1;
       if (nxt < nk) {
         int ns = stage + NS - 1;
         ns = ns >= NS ? ns - NS : ns;
-        pipe_issue<BM, A_KMAJOR, NP>(srca, nxt * stepa, lds + ns * STAGE_BYTES, pw);
-        pipe_issue<BN, B_KMAJOR, NP>(srcb, nxt * stepb, lds + ns * STAGE_BYTES + PA::BYTES, pw);
+        issue(nxt, ns);
       }
       stage = stage + 1 == NS ? 0 : stage + 1;
     }
@@ -398,69 +458,52 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_bf16_spec_kernel(G
 
   // -------------------------------------------------------------- consumer
   const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
-  f32x16_t acc[TM][TN];
+  f32x4_t acc[MB][NB];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   int stage = 0;
   for (int it = 0; it < nk; ++it) {
     __builtin_amdgcn_s_barrier();   // stage `it` is complete
     const char* ta = lds + stage * STAGE_BYTES;
-    const char* tb = ta + PA::BYTES;
-    // fragment loads run one sub-step ahead of the MFMAs that consume them
-    bf16x8_t fa[2][TM], fb[2][TN];
+    const char* tb = ta + ACH * 1024;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) fa[0][i] = pipe_fragment<BM, A_KMAJOR>(ta, wm + i * 32, 0);
+    for (int kk = 0; kk < 2; ++kk) {
+      if (kk == 1 && half_last && it == nk - 1) break;
+      bf16x8_t fa[MB], fb[NB];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) fb[0][j] = pipe_fragment<BN, B_KMAJOR>(tb, wn + j * 32, 0);
+      for (int i = 0; i < MB; ++i) fa[i] = wg_fragment<BM>(ta, wm + i * 16, kk);
 #pragma unroll
-    for (int kk = 0; kk < PBK / 16; ++kk) {
-      const int cur = kk & 1, nx = cur ^ 1;
-      if (kk + 1 < PBK / 16) {
+      for (int j = 0; j < NB; ++j) fb[j] = wg_fragment<BN>(tb, wn + j * 16, kk);
+      // operands swapped: a lane ends with output row (l & 15) and 4 consecutive columns 4*(l>>4) + r
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[nx][i] = pipe_fragment<BM, A_KMAJOR>(ta, wm + i * 32, kk + 1);
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) fb[nx][j] = pipe_fragment<BN, B_KMAJOR>(tb, wn + j * 32, kk + 1);
-      }
-      // operands swapped: a lane holds 4 consecutive output columns per register group
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
     }
     stage = stage + 1 == NS ? 0 : stage + 1;
   }
 
-  TC* __restrict__ C = (TC*)g.c;
-  bf16_t* __restrict__ AUX = (bf16_t*)g.aux;
   if (side.nonfinite) {
     // non-finite test of the weight gradients while they are still in registers (rows and columns past the edge of a
     // ragged tile repeat operand rows that also feed real outputs, so they raise the flag only when those do)
     bool bad = false;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) bad |= !(acc[i][j][r] - acc[i][j][r] == 0.f);
+        for (int r = 0; r < 4; ++r) bad |= !(acc[i][j][r] - acc[i][j][r] == 0.f);
     if (bad) *side.nonfinite = 1;   // every writer stores the same value
   }
-  // register r of lane l holds output row (l & 31), column 8*(r/4) + 4*(l/32) + r%4 of its 32x32 block
-  if constexpr (sizeof(TC) == 4) {
-    // every consumer has passed the last barrier, so the stage after the last one is read by nobody and no load
-    // is in flight to it: each wave stages its blocks in a slice of it
-    static_assert(NC * epilogue_stage32_bytes <= STAGE_BYTES, "staging exceeds a ring stage");
-    if (epilogue_can_stage32(g)) {
-      epilogue_tile32_staged<TM, TN>(g, C, acc, m0 + wm, n0 + wn, lds + stage * STAGE_BYTES + wave * epilogue_stage32_bytes);
-      return;
-    }
-  }
-  epilogue_tile32<TC, TM, TN>(g, C, AUX, acc, m0 + wm, n0 + wn);
+  // every consumer has passed the last barrier, so the stage after the last one is read by nobody and no load is in
+  // flight to it: each wave stages its blocks in a slice of it
+  static_assert(NC * epilogue_stage_f32_bytes<NB>() <= STAGE_BYTES, "staging exceeds a ring stage");
+  epilogue_tile16_f32<MB, NB>(g, (float*)g.c, acc, m0 + wm, n0 + wn,
+                              lds + stage * STAGE_BYTES + wave * epilogue_stage_f32_bytes<NB>());
 }
 
 bool launch_gemm_group_spec(const GemmDev* ds, int count, hipStream_t st, const ColsumSide* side, bool* side_taken) {
@@ -471,7 +514,7 @@ bool launch_gemm_group_spec(const GemmDev* ds, int count, hipStream_t st, const 
   grp.count = count;
   int tiles = 0;
   for (int i = 0; i < count; ++i) {
-    if (ds[i].K % PBK || ds[i].M < BM || ds[i].N < BN || (ds[i].M % 8) || (ds[i].N % 8)) return false;
+    if (ds[i].K % 32 || ds[i].M < 8 || ds[i].N < 8 || (ds[i].M % 8) || (ds[i].N % 8)) return false;
     grp.p[i] = ds[i];
     grp.tile_start[i] = tiles;
     grp.tiles_n[i] = (ds[i].N + BN - 1) / BN;
@@ -486,13 +529,12 @@ bool launch_gemm_group_spec(const GemmDev* ds, int count, hipStream_t st, const 
   for (int i = count; i < GEMM_GROUP_MAX; ++i) { grp.p[i] = grp.p[0]; grp.tiles_n[i] = 1; grp.tiles_m_first[i] = 0; }
   constexpr int LDS_BYTES = NS * (BM + BN) * PBK * 2;
   static_assert(LDS_BYTES <= 160 * 1024, "ring exceeds the LDS of a CU");
-  auto kern = gemm_bf16_spec_kernel<BM, BN, WGM, WGN, false, false, float, NS, NP>;
+  auto kern = gemm_bf16_spec_kernel<BM, BN, WGM, WGN, NS, NP>;
   static LdsLimitOnce lds_limit;   // per instantiation
   if (!lds_limit.ensure((const void*)kern, LDS_BYTES)) return false;
   const int tile_blocks = ((tiles + 7) / 8) * 8;
-  // side workers only where the tiles leave CUs free (one workgroup per CU: the ring takes most of the LDS), and
-  // enough of them that a worker's columns take less time than a tile.  With more tiles than CUs the free CUs are
-  // those of the last round: the workers come last in the grid and start when the tiles of that round have theirs.
+  // Side workers come last in the grid and so take the CUs that the last round of tiles leaves free (one workgroup per
+  // CU: the ring takes most of the LDS).
   ColsumSide sd{};
   int workers = 0;
   if (side && side->count > 0) {
@@ -500,18 +542,20 @@ bool launch_gemm_group_spec(const GemmDev* ds, int count, hipStream_t st, const 
     const int total_vecs = (side->cols[0] + side->cols[1]) / 8;
     const int last_round = tile_blocks % NUM_CUS;
     const int free_cus = last_round ? NUM_CUS - last_round : 0;
-    if (free_cus > 0 && total_vecs > 0) {
-      const int per = (total_vecs + free_cus - 1) / free_cus;
-      // per row of the contraction a worker reads per*16 bytes through registers (about 16 bytes/clock/CU: `per`
-      // clocks) while a tile needs about 30 clocks (1 us per 64-deep step, measured)
-      const bool short_enough = per <= 24;
-      const int nw = free_cus < total_vecs ? free_cus : total_vecs;
+    if (total_vecs > 0) {
+      // Per row of the contraction a worker reads per*16 bytes through registers (about 16 bytes/clock/CU: `per` clocks)
+      // while a tile needs about 30 clocks.  Where the free CUs cannot take the sums in a tile's time, all CUs take them
+      // after their tiles: at 7 vectors each for the 2048-wide layer 13 us, against 32 us for two launches of their own.
+      const bool on_free = free_cus > 0 && (total_vecs + free_cus - 1) / free_cus <= 24;
+      const int most = on_free ? free_cus : NUM_CUS;
+      const int nw = most < total_vecs ? most : total_vecs;
+      const int per = (total_vecs + nw - 1) / nw;
       bool red_ok = side->nred >= 0 && side->nred <= 3;
       for (int i = 0; red_ok && i < side->nred; ++i)
         red_ok = side->red[i].partial && side->red[i].nparts > 0 && side->red[i].ncols > 0 &&
                  side->red[i].nout >= 1 && side->red[i].nout <= 3 && side->red[i].width_out > 0 &&
                  (side->red[i].width_out + nw - 1) / nw <= THREADS;
-      if (per <= THREADS && short_enough && red_ok && (long)(THREADS / per) * per * 32 <= LDS_BYTES) {
+      if (per <= THREADS && red_ok && (long)(THREADS / per) * per * 32 <= LDS_BYTES) {
         sd = *side;
         workers = nw;
         if (side_taken) *side_taken = true;

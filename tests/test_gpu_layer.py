@@ -102,6 +102,17 @@ def test_ragged_bf16_amp(variant):
     run_and_compare(cfg, seed=3, steps=2, random_affine=True, lens_override=[160, 77, 5])
 
 
+# Weight-gradient launch at its edges: matrices smaller than one tile, contractions (batch * seq) of half a k-step, of
+# whole ones and of one half more, and 256 tiles exactly, where its side work finds no idle CU and runs after the tiles.
+# BWD_TOL covers the bf16 rounding of operands and activations; an element left out or added twice is of order one.
+@pytest.mark.parametrize("batch,seq,heads,ffn", [(1, 32, 1, 96), (3, 32, 3, 608), (1, 64, 2, 256), (2, 32, 8, 7168)])
+def test_weight_gradient_tile_edges_bf16_amp(batch, seq, heads, ffn):
+    announce("layer weight-gradient edges", batch, seq, heads, ffn)
+    cfg = dict(CONFIGS["bert_base"], batch=batch, seq=seq, hidden=64 * heads, heads=heads, ffn=ffn, len_lo=seq // 2,
+               len_hi=seq)
+    run_and_compare(cfg, seed=5, steps=1, random_affine=True)
+
+
 def test_bert_base_full_size_bf16_amp():
     announce("layer bert_base full")
     run_and_compare(CONFIGS["bert_base"], seed=0, steps=3, check_lower=True)

@@ -121,7 +121,8 @@ def test_gemm_256x256_tile_epilogues():
 
 # weight-gradient form (C = A^T B, both operands row-major over the contraction, float output) at sizes that take
 # the producer/consumer kernel: full 256x128 tiles, a partial last tile in each direction, one k-step and many
-@pytest.mark.parametrize("M,N,K", [(256, 128, 64), (768, 768, 4096), (800, 160, 320), (2304, 768, 512)])
+@pytest.mark.parametrize("M,N,K", [(256, 128, 64), (768, 768, 4096), (800, 160, 320), (2304, 768, 512),
+                                   (256, 128, 32), (288, 160, 352), (128, 128, 96)])
 def test_gemm_wgrad_form(M, N, K):
     announce("gemm-wgrad", M, N, K)
     rng = np.random.default_rng(M + 5 * N + 11 * K)
