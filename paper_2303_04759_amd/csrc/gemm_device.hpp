@@ -302,6 +302,9 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
+// s_waitcnt lgkmcnt(0): this wave's LDS reads have returned
+__device__ __forceinline__ void lds_reads_done() { __builtin_amdgcn_s_waitcnt(0xc07f); }
+
 // s_waitcnt vmcnt(n) for a wave-uniform run-time n (conservative above 24)
 __device__ __forceinline__ void wait_vmcnt_dyn(int n) {
   switch (n) {
@@ -358,8 +361,8 @@ bool launch_gemm_group_spec(const GemmDev* ds, int count, hipStream_t st, const 
                             bool* side_taken = nullptr);
 
 // Pipelined direct-to-LDS kernel family (gemm_pipe.hip).  Returns false when
-// the problem does not meet its requirements (K % 64, tile fit) and the
-// caller must use the staged kernel instead.
+// the problem does not meet its requirements (layout, bf16 output, no batch) and
+// the caller must use the staged kernel instead.
 bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32, int batch, hipStream_t st);
 
 // Full-precision products on the matrix cores (gemm_f32.hip), one problem (batched or not) of any layout, or up to

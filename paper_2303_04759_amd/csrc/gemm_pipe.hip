@@ -595,17 +595,24 @@ __device__ __forceinline__ void w48_src_init(const bf16_t* base, long ld, int ro
 }
 
 // `first` shifts the dealing so that the B chunks continue where the A chunks stopped
+__device__ __forceinline__ int kmajor_tail_shift(int q);
 template <int CHUNKS, int NW>
 __device__ __forceinline__ void w48_issue(const bf16_t* (&src)[(CHUNKS + NW - 1) / NW + 1], long koff, char* lds_tile,
-                                          int first) {
+                                          int first, bool tail) {
   const int wave = threadIdx.x >> 6;
 #pragma unroll
   for (int i = 0; i < (CHUNKS + NW - 1) / NW + 1; ++i) {
     const int q = i * NW + wave - first;
     if (q >= 0 && q < CHUNKS)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[i] + koff),
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[i] + (tail ? koff + kmajor_tail_shift(q) : koff)),
                                        (lds_void_ptr)(lds_tile + q * 1024), 16, 0, 0);
   }
+}
+
+// A contraction that ends in the middle of a k-step: in the last step the lanes whose 16-byte chunk lies in its second
+// half fetch the chunk half a step earlier instead (a valid address), and that half is not used.  q: KiB of the tile.
+__device__ __forceinline__ int kmajor_tail_shift(int q) {
+  return ((threadIdx.x & 4) != 0) == ((q & 1) == 0) ? -(PBK / 2) : 0;   // chunk (l & 7) ^ ((r >> 1) & 7), r = 8 q + l / 8
 }
 
 // 16 rows x 32 contraction values of a K-major tile: lane l holds row l&15, elements 8*(l>>4) .. +7 of k-half kk
@@ -657,12 +664,13 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS) void gemm_bf16_w48_kernel(Gemm
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int nk = g.K / PBK;
+  const int nk = (g.K + PBK - 1) / PBK;
+  const bool half_last = g.K % PBK != 0;
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
     if (s < nk) {
-      w48_issue<ACH, NW>(srca, (long)s * PBK, lds + s * STAGE_BYTES, 0);
-      w48_issue<BCH, NW>(srcb, (long)s * PBK, lds + s * STAGE_BYTES + ACH * 1024, BFIRST);
+      w48_issue<ACH, NW>(srca, (long)s * PBK, lds + s * STAGE_BYTES, 0, half_last && s == nk - 1);
+      w48_issue<BCH, NW>(srcb, (long)s * PBK, lds + s * STAGE_BYTES + ACH * 1024, BFIRST, half_last && s == nk - 1);
     }
   int stage = 0;
   for (int it = 0; it < nk; ++it) {
@@ -674,14 +682,16 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS) void gemm_bf16_w48_kernel(Gemm
       int ns = stage + NS - 1;
       ns = ns >= NS ? ns - NS : ns;
       char* nxt = lds + ns * STAGE_BYTES;
-      w48_issue<ACH, NW>(srca, (long)(it + NS - 1) * PBK, nxt, 0);
-      w48_issue<BCH, NW>(srcb, (long)(it + NS - 1) * PBK, nxt + ACH * 1024, BFIRST);
+      const bool tail = half_last && it + NS - 1 == nk - 1;
+      w48_issue<ACH, NW>(srca, (long)(it + NS - 1) * PBK, nxt, 0, tail);
+      w48_issue<BCH, NW>(srcb, (long)(it + NS - 1) * PBK, nxt + ACH * 1024, BFIRST, tail);
     }
     const char* ta = lds + stage * STAGE_BYTES;
     const char* tb = ta + ACH * 1024;
 #pragma unroll
     for (int kh = 0; kh < 2 / KS; ++kh) {
       const int kk = KS == 2 ? kg : kh;
+      if (kk == 1 && half_last && it == nk - 1) break;   // no second half
       bf16x8_t fa[4], fb[NB];
 #pragma unroll
       for (int i = 0; i < 4; ++i) fa[i] = w48_fragment(ta, wm + i * 16, kk);
@@ -759,7 +769,8 @@ __global__ __launch_bounds__(64 * (WGM * WGN * KS + NP)) void gemm_bf16_w48s_ker
   if (t >= ntile) return;
   const int m0 = (t / tiles_n) * BM, n0 = (t % tiles_n) * BN;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int nk = g.K / PBK;
+  const int nk = (g.K + PBK - 1) / PBK;
+  const bool half_last = g.K % PBK != 0;
 
   if (wave >= NC) {
     // ------------------------------------------------------------ producer
@@ -791,18 +802,19 @@ __global__ __launch_bounds__(64 * (WGM * WGN * KS + NP)) void gemm_bf16_w48s_ker
     auto issue = [&](int kstep, int stage) {
       char* base = lds + stage * STAGE_BYTES;
       const long koff = (long)kstep * PBK;
+      const bool tail = half_last && kstep == nk - 1;
 #pragma unroll
       for (int i = 0; i < LA; ++i) {
         const int q = i * NP + pw;
         if (q < ACH)
-          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srca[i] + koff),
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srca[i] + (tail ? koff + kmajor_tail_shift(q) : koff)),
                                            (lds_void_ptr)(base + q * 1024), 16, 0, 0);
       }
 #pragma unroll
       for (int i = 0; i < LB; ++i) {
         const int q = i * NP + pw - BFIRST;
         if (q >= 0 && q < BCH)
-          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcb[i] + koff),
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcb[i] + (tail ? koff + kmajor_tail_shift(q) : koff)),
                                            (lds_void_ptr)(base + (ACH + q) * 1024), 16, 0, 0);
       }
     };
@@ -847,6 +859,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN * KS + NP)) void gemm_bf16_w48s_ker
 #pragma unroll
     for (int kh = 0; kh < 2 / KS; ++kh) {
       const int kk = KS == 2 ? kg : kh;
+      if (kk == 1 && half_last && it == nk - 1) break;   // no second half
       bf16x8_t fa[4], fb[NB];
 #pragma unroll
       for (int i = 0; i < 4; ++i) fa[i] = w48_fragment(ta, wm + i * 16, kk);
@@ -952,6 +965,182 @@ static bool launch_w48_inst(const GemmDev& d, hipStream_t st) {
   return true;
 }
 
+// ---------------------------------------------------------------------------
+// Products with few output tiles (short batches, narrow layers): every wavefront
+// of a workgroup computes the whole 16 MB x 16 NB tile over its own share of the
+// contraction (k-steps w, w + NW, ...), from a ring of NS stages of its own, so
+// there is no barrier until the NW partial tiles meet in LDS.
+//
+// What bounds it: lines reach a CU at about 62 GB/s when all of them ask for new
+// ones, so a tile takes a fixed part plus 32 ps per operand row and contraction
+// value, and the tile is made as small as one round over the 256 CUs allows
+// (split_tile_choice).  All of a wavefront's stages are requested at the start:
+// with 110 to 144 KiB in flight per CU the latency of cold operands is paid once.
+// Direct loads to LDS and not register loads of the fragments: a fragment's 16
+// lanes touch 16 lines, and the address unit takes a clock for each (16 bytes per
+// clock and CU instead of 57).  Against the register-staged 128x128 kernel and the
+// rings above, cold operands: 64 x 768 x 3072 49 -> 5.8 us, 64 x 3072 x 768 15.8 ->
+// 4.7, 512 x 768 x 3072 27.7 -> 10.7, 1024 x 768 x 3072 28 -> 14.5, 1824 x 768 x 3072 27.8 -> 21.3.
+template <int MB, int NB, int NW, int NS>
+__global__ __launch_bounds__(64 * NW) void gemm_bf16_split_kernel(GemmDev g, int tiles_m, int tiles_n) {
+  constexpr int BM = 16 * MB, BN = 16 * NB, LA = 2 * MB, LB = 2 * NB;   // KiB of A and of B per stage
+  constexpr int LPS = LA + LB, STAGE_BYTES = LPS * 1024;
+  static_assert((NS - 1) * LPS <= 24, "in-flight loads exceed wait_vmcnt_dyn");
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int ntile = tiles_m * tiles_n;
+  const int per = (ntile + 7) >> 3;
+  const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);   // XCD x takes tiles [x*per, (x+1)*per)
+  if (t >= ntile) return;
+  // tiles are numbered along M first: the weights (operand B) are the larger one here, and each of their rows is then
+  // fetched by one XCD only
+  const int m0 = (t % tiles_m) * BM, n0 = (t / tiles_m) * BN;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  char* ring = lds + wave * (NS * STAGE_BYTES);
+  const bf16_t* __restrict__ A = (const bf16_t*)g.a;
+  const bf16_t* __restrict__ B = (const bf16_t*)g.b;
+  const bf16_t* srca[LA];
+  const bf16_t* srcb[LB];
+#pragma unroll
+  for (int q = 0; q < LA; ++q) {
+    const int r = q * 8 + (lane >> 3);
+    const int gr = m0 + r < g.M ? m0 + r : g.M - 1;
+    srca[q] = A + (long)gr * g.lda + (((lane & 7) ^ ((r >> 1) & 7)) << 3);
+  }
+#pragma unroll
+  for (int q = 0; q < LB; ++q) {
+    const int r = q * 8 + (lane >> 3);
+    const int gr = n0 + r < g.N ? n0 + r : g.N - 1;
+    srcb[q] = B + (long)gr * g.ldb + (((lane & 7) ^ ((r >> 1) & 7)) << 3);
+  }
+  f32x4_t acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  const int nk = (g.K + PBK - 1) / PBK;
+  const bool half_last = g.K % PBK != 0;
+  const int mine = wave < nk ? (nk - 1 - wave) / NW + 1 : 0;   // k-steps of this wavefront
+  auto issue = [&](int i, int slot) {
+    const int kstep = wave + i * NW;
+    const long koff = (long)kstep * PBK;
+    char* base = ring + slot * STAGE_BYTES;
+    const bool tail = half_last && kstep == nk - 1;
+#pragma unroll
+    for (int q = 0; q < LB; ++q)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcb[q] + (tail ? koff + kmajor_tail_shift(q) : koff)),
+                                       (lds_void_ptr)(base + (LA + q) * 1024), 16, 0, 0);
+#pragma unroll
+    for (int q = 0; q < LA; ++q)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srca[q] + (tail ? koff + kmajor_tail_shift(q) : koff)),
+                                       (lds_void_ptr)(base + q * 1024), 16, 0, 0);
+  };
+#pragma unroll
+  for (int i = 0; i < NS; ++i)
+    if (i < mine) issue(i, i);
+  int slot = 0;
+  for (int i = 0; i < mine; ++i) {
+    const int ahead = mine - 1 - i < NS - 1 ? mine - 1 - i : NS - 1;
+    wait_vmcnt_dyn(ahead * LPS);
+    asm volatile("" ::: "memory");                       // the stage is read after the wait
+    const char* ta = ring + slot * STAGE_BYTES;
+    const char* tb = ta + LA * 1024;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      if (kk == 1 && half_last && wave + i * NW == nk - 1) break;   // no second half
+      bf16x8_t fa[MB], fb[NB];
+#pragma unroll
+      for (int x = 0; x < MB; ++x) fa[x] = w48_fragment(ta, x * 16, kk);
+#pragma unroll
+      for (int y = 0; y < NB; ++y) fb[y] = w48_fragment(tb, y * 16, kk);
+      // operands swapped: a lane ends with output row (l & 15) and 4 consecutive columns 4*(l>>4) + r
+#pragma unroll
+      for (int x = 0; x < MB; ++x)
+#pragma unroll
+        for (int y = 0; y < NB; ++y)
+          acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[y], fa[x], acc[x][y], 0, 0, 0);
+    }
+    if (i + NS < mine) {
+      lds_reads_done();                                  // this wavefront's reads of the stage have returned: refill it
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      issue(i + NS, slot);
+    }
+    slot = slot + 1 == NS ? 0 : slot + 1;
+  }
+
+  // the partial tiles meet in LDS; wavefront w adds blocks w, w + NW, ... in a fixed order and finishes them
+  __syncthreads();                                       // every wavefront is done with its ring
+  f32x4_t* xch = reinterpret_cast<f32x4_t*>(lds);
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) xch[(wave * MB * NB + i * NB + j) * 64 + lane] = acc[i][j];
+  __syncthreads();
+  bf16_t* __restrict__ C = (bf16_t*)g.c;
+  bf16_t* __restrict__ AUX = (bf16_t*)g.aux;
+  epilogue_dispatch(g.epilogue, [&](auto tag) {
+    constexpr int EPI = decltype(tag)::value;
+    for (int b = wave; b < MB * NB; b += NW) {
+      f32x4_t v = xch[b * 64 + lane];
+#pragma unroll
+      for (int q = 1; q < NW; ++q) v = v + xch[(q * MB * NB + b) * 64 + lane];
+      const int row = m0 + (b / NB) * 16 + (lane & 15), col = n0 + (b % NB) * 16 + 4 * (lane >> 4);
+      if (row < g.M && col < g.N) {
+        float o[4] = {v[0], v[1], v[2], v[3]};
+        epilogue_store4<bf16_t, EPI>(g, C, AUX, row, col, o);
+      }
+    }
+  });
+}
+
+template <int MB, int NB, int NW, int NS>
+static bool launch_split_inst(const GemmDev& d, hipStream_t st) {
+  constexpr int RING_BYTES = NW * NS * 2 * (MB + NB) * 1024, XCH_BYTES = NW * MB * NB * 1024;
+  constexpr int LDS_BYTES = RING_BYTES > XCH_BYTES ? RING_BYTES : XCH_BYTES;
+  static_assert(LDS_BYTES <= 160 * 1024, "rings exceed the LDS of a CU");
+  auto kern = gemm_bf16_split_kernel<MB, NB, NW, NS>;
+  static LdsLimitOnce lds_limit;   // per instantiation
+  if (!lds_limit.ensure((const void*)kern, LDS_BYTES)) return false;
+  const int tiles_m = (d.M + 16 * MB - 1) / (16 * MB), tiles_n = (d.N + 16 * NB - 1) / (16 * NB);
+  hipLaunchKernelGGL(kern, dim3(((tiles_m * tiles_n + 7) / 8) * 8), dim3(64 * NW), LDS_BYTES, st, d, tiles_m, tiles_n);
+  return true;
+}
+
+// Run time of a tiling in picoseconds: rounds over the CUs times (fixed part of a tile + rows per contraction value).
+constexpr long CU_LINE_PS = 32;      // per operand row and contraction value, measured for every kernel of this file
+static long tiling_cost(const GemmDev& d, int bm, int bn, long fixed_ps) {
+  const long tiles = (long)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn);
+  return (tiles + 255) / 256 * (fixed_ps + CU_LINE_PS * (bm + bn) * d.K);
+}
+// The tiles of the split kernel with the fixed part of each (16x16 0.9 us ... 64x64 2.0, 64x96 5.5: six
+// blocks per wavefront to add up and store).
+struct SplitTile { int bm, bn; long fixed_ps; };
+static const SplitTile split_tiles[] = {{16, 16, 900000}, {16, 32, 1000000}, {32, 32, 1200000}, {32, 48, 1600000},
+                                        {32, 64, 1600000}, {64, 32, 1600000}, {64, 48, 1800000}, {64, 64, 2000000},
+                                        {64, 96, 5500000}};
+static int split_tile_choice(const GemmDev& d, long* cost) {
+  int best = 0;
+  for (int i = 0; i < (int)(sizeof(split_tiles) / sizeof(split_tiles[0])); ++i) {
+    const long c = tiling_cost(d, split_tiles[i].bm, split_tiles[i].bn, split_tiles[i].fixed_ps);
+    if (i == 0 || c < *cost) { best = i; *cost = c; }
+  }
+  return best;
+}
+static bool launch_split(const GemmDev& d, int choice, hipStream_t st) {
+  switch (choice) {
+    case 0: return launch_split_inst<1, 1, 8, 4>(d, st);
+    case 1: return launch_split_inst<1, 2, 8, 3>(d, st);
+    case 2: return launch_split_inst<2, 2, 8, 2>(d, st);
+    case 3: return launch_split_inst<2, 3, 8, 2>(d, st);
+    case 4: return launch_split_inst<2, 4, 4, 3>(d, st);
+    case 5: return launch_split_inst<4, 2, 4, 3>(d, st);
+    case 6: return launch_split_inst<4, 3, 4, 2>(d, st);
+    case 7: return launch_split_inst<4, 4, 4, 2>(d, st);
+    default: return launch_split_inst<4, 6, 4, 2>(d, st);
+  }
+}
+
 // 128x128 tiles, 8 wavefronts (2 x 4), two 32 KiB stages, two workgroups per CU (16 waves): the variant for a
 // K-major A with an MN-major B (products against an untransposed row-major weight, e.g. the tied decoder of the
 // MLM head) when there are enough tiles for two workgroups per CU.
@@ -961,19 +1150,10 @@ static bool launch_pipe_layout(const GemmDev& d, int batch, hipStream_t st) {
 }
 
 bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32, int batch, hipStream_t st) {
-  if (d.K % PBK) return false;
-  if (out_f32) return false;
-  // per-head attention products (N = 64, contraction <= 128): the whole problem fits the ring, so every load is
-  // issued before the first barrier instead of one memory round trip per k-step
-  if (!b_kmajor && d.N == 64 && d.K <= 2 * PBK && d.M >= 128 && d.M % 128 == 0) {
-    if (a_kmajor) return launch_pipe_inst<128, 64, 2, 2, true, false, bf16_t, 3>(d, batch, st);
-    return launch_pipe_inst<128, 64, 2, 2, false, false, bf16_t, 3>(d, batch, st);
-  }
-  if (d.M < 128 || d.N < 128 || batch != 1) return false;
-  const long tiles = (long)((d.M + 127) / 128) * ((d.N + 127) / 128);
+  if (d.K % (PBK / 2) || out_f32 || batch != 1) return false;
   if (a_kmajor && b_kmajor) {
-    // Tile choice.  Every CU has to work through ceil(tiles / 256) tiles, so the cost of a tiling is that count
-    // times the tile area; among equals the larger tile fetches fewer bytes per flop, then the squarer one.
+    // Tile choice.  Every CU has to work through ceil(tiles / 256) tiles.  With work for all CUs the cost of a tiling
+    // is that count times the tile area; among equals the larger tile fetches fewer bytes per flop, then the squarer one.
     struct Cand { int bm, bn; };
     static const Cand cands[] = {{128, 128}, {128, 96}, {128, 144}, {128, 192}, {256, 144}, {256, 192}, {256, 256}};
     int best = 0;
@@ -987,6 +1167,12 @@ bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32,
         best = i; best_cost = cost; best_area = area; best_perim = perim;
       }
     }
+    // With work for few of them the split kernel's smaller tiles win.  The line lies where its estimate meets that of
+    // the tile above, whose fixed part is about 3 us: in a step of 1824 rows the 768-deep products take 10.2 us on the
+    // rings and 13.5 on 64x96 split tiles, the 3072-deep ones 26.6 and 26.1.
+    long split_cost = 0;
+    const int split = split_tile_choice(d, &split_cost);
+    if (split_cost < tiling_cost(d, cands[best].bm, cands[best].bn, 3000000)) return launch_split(d, split, st);
     switch (best) {
       // one 128x96 tile per CU: 8 consumer + 8 producer waves, three stages (measured 24 us against 33 us for the
       // 4096x768x3072 product)
@@ -1017,7 +1203,8 @@ bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32,
   }
   // with a transposed B operand the ring only wins when there are enough tiles
   // for two workgroups per CU; below that the register-staged kernel is faster
-  if (a_kmajor && !b_kmajor && tiles >= 384) return launch_pipe_layout<true, false, bf16_t>(d, batch, st);
+  const long tiles = (long)((d.M + 127) / 128) * ((d.N + 127) / 128);
+  if (a_kmajor && !b_kmajor && d.K % PBK == 0 && d.M >= 128 && d.N >= 128 && tiles >= 384) return launch_pipe_layout<true, false, bf16_t>(d, batch, st);
   return false;
 }
 

@@ -119,6 +119,45 @@ def test_gemm_256x256_tile_epilogues():
     assert np.max(np.abs(got - ref)) <= 0.02 * (1.0 + np.max(np.abs(ref)))
 
 
+# Few output tiles: the sizes take each tile of the split kernel (16x16, 16x32, 32x32, 32x48, 32x64, 64x32, 64x48, 64x64,
+# 64x96), with ragged last tiles, contractions shorter than the wavefronts' shares and ones that end in half a k-step;
+# then every tile of the rings with such a contraction.  Bound per element: bf16 rounding of the result (2^-9 relative,
+# twice that for the stored pre-activation path) and float32 accumulation of K products.
+@pytest.mark.parametrize("epi", ["bias", "gelu_pair", "residual"])
+@pytest.mark.parametrize("M,N,K", [(32, 32, 32), (64, 768, 800), (128, 768, 352), (256, 768, 800), (96, 3072, 96),
+                                   (480, 1056, 352), (1056, 480, 352), (992, 736, 1056), (992, 1024, 1056),
+                                   (992, 1440, 1568), (4064, 768, 96), (1984, 2304, 96), (8160, 768, 96),
+                                   (3968, 2304, 96), (3968, 3072, 96), (2016, 8192, 96), (4064, 1024, 96),
+                                   (3968, 3072, 1568)])
+def test_gemm_split_tiles_and_half_steps(M, N, K, epi):
+    announce("gemm-split", M, N, K, epi)
+    rng = np.random.default_rng(M + 3 * N + 7 * K)
+    A, W = rnd(rng, (M, K), 1), rnd(rng, (N, K), 1, 0.1)
+    bias = rng.standard_normal(N).astype(np.float32)
+    a_dev, w_dev, b_dev = to_dev(A, torch.bfloat16), to_dev(W, torch.bfloat16), torch.from_numpy(bias).cuda()
+    lin = A.astype(np.float64) @ W.astype(np.float64).T
+    slack = K * 2.0 ** -24 * (np.abs(A).astype(np.float64) @ np.abs(W).astype(np.float64).T) + 1e-6
+    c = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+
+    def check(ref, extra=0.0):
+        err = np.abs(host(c) - ref)
+        assert (err <= 2.0 ** -8 * np.abs(ref) + slack + extra).all(), float(err.max())
+    if epi == "bias":
+        raf.raf_op_gemm(1, M, N, K, a_dev, K, 1, w_dev, K, 1, c, N, epilogue=raf.EPI_BIAS, bias=b_dev)
+        check(lin + bias)
+    elif epi == "gelu_pair":
+        # the fast erf form: |gelu error| <= 2.6e-5 (times |u| <= 40 here), gelu' is read back and applied
+        d = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        raf.raf_op_gemm(1, M, N, K, a_dev, K, 1, w_dev, K, 1, c, N, epilogue=raf.EPI_BIAS_GELU_DERIV, bias=b_dev, aux=d)
+        check(L.gelu(lin + bias, False), 2e-3)
+        raf.raf_op_gemm(1, M, N, K, a_dev, K, 1, w_dev, K, 1, c, N, epilogue=raf.EPI_MUL_AUX, aux=d)
+        check(lin * host(d))
+    else:
+        R = rnd(rng, (M, N), 1)
+        raf.raf_op_gemm(1, M, N, K, a_dev, K, 1, w_dev, K, 1, c, N, epilogue=raf.EPI_ADD_RES, aux=to_dev(R, torch.bfloat16))
+        check(lin + R)
+
+
 # weight-gradient form (C = A^T B, both operands row-major over the contraction, float output) at sizes that take
 # the producer/consumer kernel: full 256x128 tiles, a partial last tile in each direction, one k-step and many
 @pytest.mark.parametrize("M,N,K", [(256, 128, 64), (768, 768, 4096), (800, 160, 320), (2304, 768, 512),
