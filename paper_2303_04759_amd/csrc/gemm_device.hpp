@@ -37,10 +37,12 @@ __device__ __forceinline__ void store4(float* p, const float (&v)[4]) {
   *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// The epilogue kind is a template parameter here and the kernels switch on it once, outside their unrolled store
-// loops: with the run-time switch inside, every one of the 12-64 store groups of a wave carried all cases and the
-// epilogue of the plain-bias GEMMs slowed down by several microseconds when a case was added.
-template <typename TC, int EPI>
+// The epilogue kind and the form of GeLU are template parameters here and the kernels switch on them once, outside
+// their unrolled store loops: a test of the form per element kept the elements' chains from overlapping (with the
+// cheaper reciprocal 4096 x 3072 x 768 with GeLU and derivative 37.4 -> 34.5 us on 16 wavefronts, 4096 x 8192 x 2048
+// 158 -> 152), and with the run-time switch of the kind inside, every one of the 12-64 store groups of a wave carried
+// all cases and the epilogue of the plain-bias GEMMs slowed down by several microseconds when a case was added.
+template <typename TC, int EPI, int TANH>
 __device__ __forceinline__ void epilogue_store4(const GemmDev& g, TC* __restrict__ c, bf16_t* __restrict__ aux, int i,
                                                 int j, float (&v)[4]) {
 #pragma unroll
@@ -53,12 +55,12 @@ __device__ __forceinline__ void epilogue_store4(const GemmDev& g, TC* __restrict
     store4(aux + (long)i * g.ldaux + j, v);
     // GeLU is evaluated on the value the backward pass will read back
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = gelu_f((float)(bf16_t)v[e], g.gelu_tanh);
+    for (int e = 0; e < 4; ++e) v[e] = gelu_f((float)(bf16_t)v[e], TANH);
   } else if constexpr (EPI == EPI_MUL_GELU_GRAD) {
     float u[4];
     load4(aux + (long)i * g.ldaux + j, u);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_f(u[e], g.gelu_tanh);
+    for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_f(u[e], TANH);
   } else if constexpr (EPI == EPI_ADD_RES) {
     float r[4];
     load4(aux + (long)i * g.ldaux + j, r);
@@ -67,7 +69,7 @@ __device__ __forceinline__ void epilogue_store4(const GemmDev& g, TC* __restrict
   } else if constexpr (EPI == EPI_BIAS_GELU_DERIV) {
     float dy[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) gelu_and_grad_f(v[e], g.gelu_tanh, v[e], dy[e]);
+    for (int e = 0; e < 4; ++e) gelu_and_grad_f(v[e], TANH, v[e], dy[e]);
     store4(aux + (long)i * g.ldaux + j, dy);
   } else if constexpr (EPI == EPI_MUL_AUX) {
     float r[4];
@@ -83,15 +85,26 @@ struct EpiTag {
   static constexpr int value = V;
 };
 template <typename F>
-__device__ __forceinline__ void epilogue_dispatch(int epi, F&& f) {
-  switch (epi) {
-    case EPI_BIAS: f(EpiTag<EPI_BIAS>{}); break;
-    case EPI_BIAS_GELU: f(EpiTag<EPI_BIAS_GELU>{}); break;
-    case EPI_MUL_GELU_GRAD: f(EpiTag<EPI_MUL_GELU_GRAD>{}); break;
-    case EPI_ADD_RES: f(EpiTag<EPI_ADD_RES>{}); break;
-    case EPI_BIAS_GELU_DERIV: f(EpiTag<EPI_BIAS_GELU_DERIV>{}); break;
-    case EPI_MUL_AUX: f(EpiTag<EPI_MUL_AUX>{}); break;
-    default: f(EpiTag<EPI_NONE>{}); break;
+__device__ __forceinline__ void epilogue_dispatch(const GemmDev& g, F&& f) {
+  constexpr EpiTag<0> erf_form{};
+  constexpr EpiTag<1> tanh_form{};
+  switch (g.epilogue) {
+    case EPI_BIAS: f(EpiTag<EPI_BIAS>{}, erf_form); break;
+    case EPI_BIAS_GELU:
+      if (g.gelu_tanh) f(EpiTag<EPI_BIAS_GELU>{}, tanh_form);
+      else f(EpiTag<EPI_BIAS_GELU>{}, erf_form);
+      break;
+    case EPI_MUL_GELU_GRAD:
+      if (g.gelu_tanh) f(EpiTag<EPI_MUL_GELU_GRAD>{}, tanh_form);
+      else f(EpiTag<EPI_MUL_GELU_GRAD>{}, erf_form);
+      break;
+    case EPI_ADD_RES: f(EpiTag<EPI_ADD_RES>{}, erf_form); break;
+    case EPI_BIAS_GELU_DERIV:
+      if (g.gelu_tanh) f(EpiTag<EPI_BIAS_GELU_DERIV>{}, tanh_form);
+      else f(EpiTag<EPI_BIAS_GELU_DERIV>{}, erf_form);
+      break;
+    case EPI_MUL_AUX: f(EpiTag<EPI_MUL_AUX>{}, erf_form); break;
+    default: f(EpiTag<EPI_NONE>{}, erf_form); break;
   }
 }
 
@@ -101,8 +114,8 @@ template <typename TC, int TM, int TN>
 __device__ __forceinline__ void epilogue_tile32(const GemmDev& g, TC* __restrict__ C, bf16_t* __restrict__ AUX,
                                                 f32x16_t (&acc)[TM][TN], int row0, int col0) {
   const int lane = threadIdx.x & 63;
-  epilogue_dispatch(g.epilogue, [&](auto tag) {
-    constexpr int EPI = decltype(tag)::value;
+  epilogue_dispatch(g, [&](auto tag, auto form) {
+    constexpr int EPI = decltype(tag)::value, TANH = decltype(form)::value;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int row = row0 + i * 32 + (lane & 31);
@@ -114,7 +127,7 @@ __device__ __forceinline__ void epilogue_tile32(const GemmDev& g, TC* __restrict
             const int col = col0 + j * 32 + 8 * q + 4 * (lane >> 5);
             if (col < g.N) {
               float v[4] = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-              epilogue_store4<TC, EPI>(g, C, AUX, row, col, v);
+              epilogue_store4<TC, EPI, TANH>(g, C, AUX, row, col, v);
             }
           }
       }
@@ -128,8 +141,8 @@ template <typename TC, int NB>
 __device__ __forceinline__ void epilogue_tile16(const GemmDev& g, TC* __restrict__ C, bf16_t* __restrict__ AUX,
                                                 f32x4_t (&acc)[4][NB], int row0, int col0, int i_begin, int i_end) {
   const int lane = threadIdx.x & 63;
-  epilogue_dispatch(g.epilogue, [&](auto tag) {
-    constexpr int EPI = decltype(tag)::value;
+  epilogue_dispatch(g, [&](auto tag, auto form) {
+    constexpr int EPI = decltype(tag)::value, TANH = decltype(form)::value;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (i < i_begin || i >= i_end) continue;
@@ -140,7 +153,7 @@ __device__ __forceinline__ void epilogue_tile16(const GemmDev& g, TC* __restrict
           const int col = col0 + j * 16 + 4 * (lane >> 4);
           if (col < g.N) {
             float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-            epilogue_store4<TC, EPI>(g, C, AUX, row, col, v);
+            epilogue_store4<TC, EPI, TANH>(g, C, AUX, row, col, v);
           }
         }
       }
@@ -177,8 +190,8 @@ __device__ __forceinline__ void epilogue_tile16_staged(const GemmDev& g, bf16_t*
   constexpr int CPR = 2 * NB;             // 16-byte pieces per row
   const int lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
-  epilogue_dispatch(g.epilogue, [&](auto tag) {
-    constexpr int EPI = decltype(tag)::value;
+  epilogue_dispatch(g, [&](auto tag, auto form) {
+    constexpr int EPI = decltype(tag)::value, TANH = decltype(form)::value;
     constexpr bool AUX_IN = EPI == EPI_MUL_GELU_GRAD || EPI == EPI_ADD_RES || EPI == EPI_MUL_AUX;
     constexpr bool AUX_OUT = EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_GELU_DERIV;
     constexpr bool BIAS = EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_GELU_DERIV;
@@ -237,23 +250,25 @@ __device__ __forceinline__ void epilogue_tile16_staged(const GemmDev& g, bf16_t*
             store4(reinterpret_cast<bf16_t*>(s_aux + off), v);
             // GeLU is evaluated on the value the backward pass will read back
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = gelu_fast((float)(bf16_t)v[e], g.gelu_tanh);
+            for (int e = 0; e < 4; ++e) v[e] = gelu_fast((float)(bf16_t)v[e], TANH);
           } else if constexpr (EPI == EPI_BIAS_GELU_DERIV) {
             float dy[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) gelu_and_grad_fast(v[e], g.gelu_tanh, v[e], dy[e]);
+            for (int e = 0; e < 4; ++e) gelu_and_grad_fast(v[e], TANH, v[e], dy[e]);
             store4(reinterpret_cast<bf16_t*>(s_aux + off), dy);
           } else if constexpr (AUX_IN) {
             float u[4];
             load4(reinterpret_cast<const bf16_t*>(s_aux + off), u);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              if constexpr (EPI == EPI_MUL_GELU_GRAD) v[e] *= gelu_grad_fast(u[e], g.gelu_tanh);
+              if constexpr (EPI == EPI_MUL_GELU_GRAD) v[e] *= gelu_grad_fast(u[e], TANH);
               else if constexpr (EPI == EPI_ADD_RES) v[e] += u[e];
               else v[e] *= u[e];
             }
           }
           store4(reinterpret_cast<bf16_t*>(s_out + off), v);
+          // four chains at a time: with all of a trip's in flight at once some instantiations spill registers
+          if constexpr (AUX_OUT || EPI == EPI_MUL_GELU_GRAD) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
       for (int it = 0; it < IT; ++it) {

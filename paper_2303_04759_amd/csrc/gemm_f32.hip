@@ -68,7 +68,7 @@ __device__ __forceinline__ f32x4_t f32_fragment(const char* p) {
 }
 
 // columns j .. j+3 of row i, epilogue resolved at compile time
-template <int EPI>
+template <int EPI, int TANH>
 __device__ __forceinline__ void f32_epilogue_store4(const GemmDev& g, float* __restrict__ c, float* __restrict__ aux, int i,
                                                     int j, f32x4_t v) {
   v = v * g.alpha;
@@ -80,13 +80,13 @@ __device__ __forceinline__ void f32_epilogue_store4(const GemmDev& g, float* __r
   if constexpr (EPI == EPI_BIAS_GELU) {
     *ax = v;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = gelu_f(v[e], g.gelu_tanh);
+    for (int e = 0; e < 4; ++e) v[e] = gelu_f(v[e], TANH);
   } else if constexpr (EPI == EPI_BIAS_GELU_DERIV) {
     f32x4_t dy;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float y, d;
-      gelu_and_grad_f(v[e], g.gelu_tanh, y, d);
+      gelu_and_grad_f(v[e], TANH, y, d);
       v[e] = y;
       dy[e] = d;
     }
@@ -94,7 +94,7 @@ __device__ __forceinline__ void f32_epilogue_store4(const GemmDev& g, float* __r
   } else if constexpr (EPI == EPI_MUL_GELU_GRAD) {
     const f32x4_t u = *ax;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_f(u[e], g.gelu_tanh);
+    for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_f(u[e], TANH);
   } else if constexpr (EPI == EPI_ADD_RES) {
     v = v + *ax;
   } else if constexpr (EPI == EPI_MUL_AUX) {
@@ -214,14 +214,14 @@ __device__ __forceinline__ void f32_tile(const GemmDev& g, int m0, int n0, int z
 #pragma unroll
     for (int j = 0; j < NB; ++j) xch[((long)kg * NT * MB * NB + i * NB + j) * 64 + lane] = acc[i][j];
   __syncthreads();
-  epilogue_dispatch(g.epilogue, [&](auto tag) {
-    constexpr int EPI = decltype(tag)::value;
+  epilogue_dispatch(g, [&](auto tag, auto form) {
+    constexpr int EPI = decltype(tag)::value, TANH = decltype(form)::value;
     for (int b = kg; b < MB * NB; b += KS) {
       f32x4_t v = xch[(long)b * 64 + lane];
 #pragma unroll
       for (int s = 1; s < KS; ++s) v = v + xch[((long)s * NT * MB * NB + b) * 64 + lane];
       const int row = m0 + wm + (b / NB) * 16 + (lane & 15), col = n0 + wn + (b % NB) * 16 + 4 * (lane >> 4);
-      if (row < g.M && col < g.N) f32_epilogue_store4<EPI>(g, C, AUX, row, col, v);
+      if (row < g.M && col < g.N) f32_epilogue_store4<EPI, TANH>(g, C, AUX, row, col, v);
     }
   });
 }

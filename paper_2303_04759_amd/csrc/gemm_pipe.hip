@@ -1091,8 +1091,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_split_kernel(GemmDev g, int
   __syncthreads();
   bf16_t* __restrict__ C = (bf16_t*)g.c;
   bf16_t* __restrict__ AUX = (bf16_t*)g.aux;
-  epilogue_dispatch(g.epilogue, [&](auto tag) {
-    constexpr int EPI = decltype(tag)::value;
+  epilogue_dispatch(g, [&](auto tag, auto form) {
+    constexpr int EPI = decltype(tag)::value, TANH = decltype(form)::value;
     for (int b = wave; b < MB * NB; b += NW) {
       f32x4_t v = xch[b * 64 + lane];
 #pragma unroll
@@ -1100,7 +1100,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_split_kernel(GemmDev g, int
       const int row = m0 + (b / NB) * 16 + (lane & 15), col = n0 + (b % NB) * 16 + 4 * (lane >> 4);
       if (row < g.M && col < g.N) {
         float o[4] = {v[0], v[1], v[2], v[3]};
-        epilogue_store4<bf16_t, EPI>(g, C, AUX, row, col, o);
+        epilogue_store4<bf16_t, EPI, TANH>(g, C, AUX, row, col, o);
       }
     }
   });

@@ -158,6 +158,27 @@ def test_gemm_split_tiles_and_half_steps(M, N, K, epi):
         check(lin + R)
 
 
+def test_gemm_gelu_epilogue_at_the_ends_of_the_range():
+    """GeLU and its derivative far from zero, at infinity and at nan: rows of zeros, so that u is the bias."""
+    announce("gemm-gelu-range")
+    M = N = K = 64
+    bf = torch.bfloat16
+    bias = torch.zeros(N)
+    bias[:7] = torch.tensor([1e4, -1e4, 1e30, -1e30, float("inf"), float("nan"), 3e38])
+    a = torch.zeros(M, K, dtype=bf, device="cuda")
+    for tanh in (0, 1):
+        c, d = (torch.zeros(M, N, dtype=bf, device="cuda") for _ in range(2))
+        raf.raf_op_gemm(1, M, N, K, a, K, 1, a, K, 1, c, N, epilogue=raf.EPI_BIAS_GELU_DERIV, bias=bias.cuda(), aux=d,
+                        gelu_tanh=tanh)
+        y, dy = host(c)[0], host(d)[0]
+        want = bias.to(bf).double().numpy()
+        assert np.array_equal(y[[0, 2, 4]], want[[0, 2, 4]]) and y[1] == 0 and np.isnan(y[5])
+        assert dy[0] == 1 and dy[1] == 0 and np.isnan(dy[5])
+        if not tanh:   # the tanh form's cubes overflow
+            assert y[3] == 0 and dy[2] == 1 and dy[3] == 0 and y[6] == want[6] and dy[6] == 1
+        assert np.array_equal(y[7:], np.zeros(N - 7)) and np.all(dy[7:] == 0.5)
+
+
 # weight-gradient form (C = A^T B, both operands row-major over the contraction, float output) at sizes that take
 # the producer/consumer kernel: full 256x128 tiles, a partial last tile in each direction, one k-step and many
 @pytest.mark.parametrize("M,N,K", [(256, 128, 64), (768, 768, 4096), (800, 160, 320), (2304, 768, 512),
