@@ -978,6 +978,267 @@ static bool launch_w48_inst(const GemmDev& d, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
+// Large tiles on eight wavefronts in two groups of four, one of each per SIMD: while one group issues its 16 (12) MFMAs
+// of a phase, the other reads the fragments of its next phase from LDS and requests its next operand pieces, and a
+// barrier swaps the roles.  A wave tile is split in 2 x 2 quadrants and a k-step in four phases (quadrant 00: reads the
+// upper half of the A fragments and the left half of the B ones, 01: the right half of B, 11: the lower half of A, 10:
+// nothing), and each half of an operand tile has a buffer of its own in each of the two stages: it is free
+// again as soon as its one phase is over, so its next filling is requested ten half-phases (about 1.2 us) before it is
+// waited for and the ring needs no third stage.
+//
+// What bounds it: per k-step a 256x256 tile takes 2048 clocks of MFMA and the loop about 2800; 8192 x 8192 x 8192 runs at
+// 1.57 PFLOP/s (699 us; 912 with 16 symmetric wavefronts that read, request and multiply in turn).  Short contractions
+// are bound by the fixed part of 8 us: first stages, and an epilogue of all CUs at once.  Measured against the kernels
+// that had these shapes (128x128 producer/consumer tiles, 256x192 and 256x256 tiles): 4096 x 6144 x 2048 113.6 -> 86.7
+// us, 4096 x 8192 x 2048 125.9 -> 100.2, 4096 x 2048 x 8192 147.8 -> 109.2, 4096 x 2048 x 2048 43.4 -> 33.5, 8192 x 3072 x
+// 768 51.9 -> 43.4, 4096 x 4096 x 1024 33.1 -> 30.7, 896 x 30528 x 768 76.5 -> 48.5 (cold operands).  Requests by buffer
+// loads (scalar k offset) instead of 64-bit addresses: 8192 x 8192 x 8192 727 -> 699; reading all of a quadrant row's
+// fragments in one phase, and waiting for them before the swap: 749.
+template <int WGM, int WGN, int MH, int NH>   // waves along M and N, 16x16 blocks of a quadrant along M and N
+struct PingPong {
+  static constexpr int BM = 32 * MH * WGM, BN = 32 * NH * WGN;
+  static constexpr int ACH = BM / 16, BCH = BN / 16;      // KiB (8 rows x 64 values) of half an operand tile
+  static constexpr int STAGE = (2 * ACH + 2 * BCH) * 1024;
+  static constexpr int LDS_BYTES = 2 * STAGE;
+  static_assert(WGM * WGN == 8, "two groups of four wavefronts");
+  static_assert(ACH % 8 == 0 && BCH % 4 == 0, "half tiles deal evenly to the wavefronts of a group");
+};
+
+template <int WGM, int WGN, int MH, int NH, bool HALF>
+__global__ __launch_bounds__(512) void gemm_bf16_pingpong_kernel(GemmDev g, int tiles_m, int tiles_n) {
+  typedef PingPong<WGM, WGN, MH, NH> PP;
+  constexpr int BM = PP::BM, BN = PP::BN, ACH = PP::ACH, BCH = PP::BCH, STAGE = PP::STAGE;
+  constexpr int LA = ACH / 8, LB = (BCH + 7) / 8;        // loads per wavefront of half a tile (B: at most)
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+
+  // XCD x takes tiles [x*per, (x+1)*per) of a list that runs down 4 rows of tiles before it steps to the next column:
+  // the 32 tiles that an XCD works on at a time then share 4 + 8 operand panels instead of 1 + 32
+  const int ntile = tiles_m * tiles_n;
+  const int per = (ntile + 7) >> 3;
+  const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if (t >= ntile) return;
+  const int grp = t / (4 * tiles_n), in_grp = t - grp * 4 * tiles_n;
+  const int rows = tiles_m - 4 * grp < 4 ? tiles_m - 4 * grp : 4;
+  // (the divisions run in vector registers: back to scalar ones)
+  const int m0 = __builtin_amdgcn_readfirstlane((4 * grp + in_grp % rows) * BM);
+  const int n0 = __builtin_amdgcn_readfirstlane((in_grp / rows) * BN);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wr = wave / WGN, wc = wave % WGN;
+  const int nk = HALF ? g.K / PBK + 1 : g.K / PBK;
+
+  // Half h of the A tile holds, for every row of waves, the 16 MH rows of quadrant row h; of the B tile likewise.
+  // Per-lane source offsets of this wave's KiB pieces (one piece: 8 rows of 128 bytes, chunk c of row r at c ^ ((r >> 1) & 7)).
+  // Buffer loads: the k-step is a scalar offset, so a request costs no vector instruction and no address register.
+  const int ma = g.M - m0 < BM ? g.M - m0 : BM, mb = g.N - n0 < BN ? g.N - n0 : BN;   // rows of the panels
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)g.a + (long)m0 * g.lda * 2), 0,
+                                                                      ((ma - 1) * g.lda + g.K) * 2, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)g.b + (long)n0 * g.ldb * 2), 0,
+                                                                      ((mb - 1) * g.ldb + g.K) * 2, 0x00020000);
+  uint32_t offa[2][LA], offb[2][LB];
+  const int c8 = lane & 7;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+      const int r = (i * 8 + wave) * 8 + (lane >> 3);    // row within the half
+      int row = (r / (16 * MH)) * 32 * MH + h * 16 * MH + r % (16 * MH);
+      row = row < ma ? row : ma - 1;
+      offa[h][i] = (uint32_t)row * (uint32_t)(g.lda * 2) + ((c8 ^ ((r >> 1) & 7)) << 4);
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+      int q = i * 8 + wave;
+      q = q < BCH ? q : BCH - 1;
+      const int r = q * 8 + (lane >> 3);
+      int row = (r / (16 * NH)) * 32 * NH + h * 16 * NH + r % (16 * NH);
+      row = row < mb ? row : mb - 1;
+      offb[h][i] = (uint32_t)row * (uint32_t)(g.ldb * 2) + ((c8 ^ ((r >> 1) & 7)) << 4);
+    }
+  }
+  // requests half h of the A (B) tile of k-step `kstep` into stage s = kstep & 1
+  auto load_a = [&](int h, int kstep, int s) {
+    char* dst = lds + s * STAGE + h * ACH * 1024;
+    const bool tail = HALF && kstep == nk - 1;
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+      const int q = i * 8 + wave;
+      const uint32_t off = tail ? offa[h][i] + 2 * kmajor_tail_shift(q) : offa[h][i];
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_ptr)(dst + q * 1024), 16, off, kstep * (PBK * 2), 0, 0);
+    }
+  };
+  auto load_b = [&](int h, int kstep, int s) {
+    char* dst = lds + s * STAGE + (2 * ACH + h * BCH) * 1024;
+    const bool tail = HALF && kstep == nk - 1;
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+      const int q = i * 8 + wave;
+      if (i * 8 + 8 <= BCH || q < BCH) {
+        const uint32_t off = tail ? offb[h][i] + 2 * kmajor_tail_shift(q) : offb[h][i];
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void_ptr)(dst + q * 1024), 16, off, kstep * (PBK * 2), 0, 0);
+      }
+    }
+  };
+
+  f32x4_t acc[2][2][MH][NH];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int i = 0; i < MH; ++i)
+#pragma unroll
+        for (int j = 0; j < NH; ++j) acc[x][y][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  bf16x8_t fa[2][MH], fb[2][2][NH];     // A: k-half, block; B: column half, k-half, block
+  auto read_a = [&](int h, int s) {
+    const char* tile = lds + s * STAGE + h * ACH * 1024;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int i = 0; i < MH; ++i) fa[kk][i] = w48_fragment(tile, wr * 16 * MH + i * 16, kk);
+  };
+  auto read_b = [&](int h, int s) {
+    const char* tile = lds + s * STAGE + (2 * ACH + h * BCH) * 1024;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int j = 0; j < NH; ++j) fb[h][kk][j] = w48_fragment(tile, wc * 16 * NH + j * 16, kk);
+  };
+  auto swap_roles = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the products of quadrant (x, y); the compiler waits for the fragments, whose reads were issued before the swap
+  auto products = [&](int x, int y, bool both) {
+    swap_roles();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      if (HALF && kk == 1 && !both) break;
+      // operands swapped: a lane ends with output row (l & 15) and 4 consecutive columns 4*(l>>4) + r
+#pragma unroll
+      for (int i = 0; i < MH; ++i)
+#pragma unroll
+        for (int j = 0; j < NH; ++j)
+          acc[x][y][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[y][kk][j], fa[kk][i], acc[x][y][i][j], 0, 0, 0);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    swap_roles();
+  };
+  // loads of this wave per half tile of B (the second group may have one less)
+  const int lb = BCH % 8 ? (wave < BCH % 8 ? LB : LB - 1) : LB;
+  auto wait_halves = [&](auto na, auto nb) {   // that many halves of A and of B may stay in flight
+    constexpr int NA = decltype(na)::value, NBH = decltype(nb)::value;
+    if constexpr (BCH % 8 == 0) wait_vmcnt<NA * LA + NBH * LB>();
+    else if (lb == LB) wait_vmcnt<NA * LA + NBH * LB>();
+    else wait_vmcnt<NA * LA + NBH * (LB - 1)>();
+  };
+  constexpr EpiTag<0> n0h{}; constexpr EpiTag<1> n1h{}; constexpr EpiTag<2> n2h{}; constexpr EpiTag<3> n3h{};
+
+  // k-step `it` of parity F.  Quadrants (0,F) (0,1-F) (1,1-F) (1,F): the last phase leaves the registers of B half 1-F
+  // free for the fragments that k-step it + 1 starts with, so that no phase reads more than 2 MH fragments.  A half
+  // buffer is refilled two swaps or more after its last read was issued: all its reads have returned by then (each
+  // wave's products waited for them).  Order of a wave's requests: B[F] A[0] B[1-F] A[1] of each k-step; every wait
+  // leaves the last five (fewer at the end) in flight and is for what the next phase reads.
+  auto kstep = [&](auto parity, int it, int rest) {
+    constexpr int F = decltype(parity)::value;
+    const bool both = !HALF || rest > 0;
+    read_a(0, F);
+    if (rest >= 1) {
+      load_a(1, it + 1, 1 - F);
+      wait_halves(n3h, n2h);                    // B[1-F] of this k-step
+    } else {
+      wait_halves(n1h, n0h);
+    }
+    products(0, F, both);
+    read_b(1 - F, F);
+    if (rest >= 2) {
+      load_b(F, it + 2, F);
+      wait_halves(n2h, n3h);                    // A[1]
+    } else if (rest == 1) {
+      wait_halves(n2h, n2h);
+    } else {
+      wait_halves(n0h, n0h);
+    }
+    products(0, 1 - F, both);
+    read_a(1, F);
+    if (rest >= 2) {
+      load_a(0, it + 2, F);
+      wait_halves(n3h, n2h);                    // B[1-F] of the next k-step
+    } else {
+      wait_halves(n2h, n1h);
+    }
+    products(1, 1 - F, both);
+    if (rest >= 1) read_b(1 - F, 1 - F);
+    if (rest >= 2) {
+      load_b(1 - F, it + 2, F);
+      wait_halves(n2h, n3h);                    // A[0] of the next k-step
+    } else {
+      wait_halves(n1h, n1h);
+    }
+    products(1, F, both);
+  };
+  load_b(0, 0, 0); load_a(0, 0, 0); load_b(1, 0, 0); load_a(1, 0, 0);
+  load_b(1, 1, 1); load_a(0, 1, 1); load_b(0, 1, 1);
+  wait_halves(n2h, n3h);                        // B[0] and A[0] of k-step 0 have landed
+  __builtin_amdgcn_s_barrier();
+  read_b(0, 0);
+  if (wave >= 4) swap_roles();                  // the second group runs half a phase behind
+  __builtin_amdgcn_sched_barrier(0);
+
+  int it = 0;
+  for (; it + 3 < nk; it += 2) {                // without the tests for the end
+    kstep(n0h, it, 2);
+    kstep(n1h, it + 1, 2);
+  }
+  for (; it < nk; it += 2) {
+    kstep(n0h, it, nk - 1 - it);
+    if (it + 1 < nk) kstep(n1h, it + 1, nk - 2 - it);
+  }
+  if (wave < 4) swap_roles();
+
+  // every fragment read and every load of the workgroup is over: the waves stage their blocks in slices of the ring
+  constexpr int SB = epilogue_stage_bytes<2 * NH>();
+  static_assert(8 * SB <= PP::LDS_BYTES, "staging exceeds the ring");
+  char* stg = lds + wave * SB;
+  bf16_t* __restrict__ C = (bf16_t*)g.c;
+  bf16_t* __restrict__ AUX = (bf16_t*)g.aux;
+  const int row0 = m0 + wr * 32 * MH, col0 = n0 + wc * 32 * NH;
+  // 64 rows of the wave tile.  Inlined by force: as a function of its own it gets the kernel's state through memory, and
+  // branches too far for one instruction use the registers that hold its return address.
+  auto band = [&](auto tag) __attribute__((always_inline)) {
+    constexpr int I0 = decltype(tag)::value * 4;
+    f32x4_t out[4][2 * NH];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2 * NH; ++j) out[i][j] = acc[(I0 + i) / MH][j / NH][(I0 + i) % MH][j % NH];
+    if (epilogue_can_stage(g)) epilogue_tile16_staged<2 * NH>(g, C, AUX, out, row0 + I0 * 16, col0, 0, 4, stg);
+    else epilogue_tile16<bf16_t, 2 * NH>(g, C, AUX, out, row0 + I0 * 16, col0, 0, 4);
+  };
+  static_assert(MH == 2 || MH == 4, "one or two bands");
+  band(EpiTag<0>{});
+  if constexpr (MH == 4) band(EpiTag<1>{});
+}
+
+template <int WGM, int WGN, int MH, int NH, bool HALF>
+static bool launch_pingpong_half(const GemmDev& d, hipStream_t st) {
+  typedef PingPong<WGM, WGN, MH, NH> PP;
+  auto kern = gemm_bf16_pingpong_kernel<WGM, WGN, MH, NH, HALF>;
+  static LdsLimitOnce lds_limit;   // per instantiation
+  if (!lds_limit.ensure((const void*)kern, PP::LDS_BYTES)) return false;
+  const int tiles_m = (d.M + PP::BM - 1) / PP::BM, tiles_n = (d.N + PP::BN - 1) / PP::BN;
+  hipLaunchKernelGGL(kern, dim3(((tiles_m * tiles_n + 7) / 8) * 8), dim3(512), PP::LDS_BYTES, st, d, tiles_m, tiles_n);
+  return true;
+}
+template <int WGM, int WGN, int MH, int NH>
+static bool launch_pingpong_inst(const GemmDev& d, hipStream_t st) {
+  return d.K % PBK ? launch_pingpong_half<WGM, WGN, MH, NH, true>(d, st)
+                   : launch_pingpong_half<WGM, WGN, MH, NH, false>(d, st);
+}
+
+// ---------------------------------------------------------------------------
 // Products with few output tiles (short batches, narrow layers): every wavefront
 // of a workgroup computes the whole 16 MB x 16 NB tile over its own share of the
 // contraction (k-steps w, w + NW, ...), from a ring of NS stages of its own, so
@@ -993,7 +1254,7 @@ static bool launch_w48_inst(const GemmDev& d, hipStream_t st) {
 // clock and CU instead of 57).  Against the register-staged 128x128 kernel and the
 // rings above, cold operands: 64 x 768 x 3072 49 -> 5.8 us, 64 x 3072 x 768 15.8 ->
 // 4.7, 512 x 768 x 3072 27.7 -> 10.7, 1024 x 768 x 3072 28 -> 14.5, 1824 x 768 x 3072 27.8 -> 21.3.
-template <int MB, int NB, int NW, int NS>
+template <int MB, int NB, int NW, int NS, bool HALF>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_split_kernel(GemmDev g, int tiles_m, int tiles_n) {
   constexpr int BM = 16 * MB, BN = 16 * NB, LA = 2 * MB, LB = 2 * NB;   // KiB of A and of B per stage
   constexpr int LPS = LA + LB, STAGE_BYTES = LPS * 1024;
@@ -1030,14 +1291,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_split_kernel(GemmDev g, int
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int nk = (g.K + PBK - 1) / PBK;
-  const bool half_last = g.K % PBK != 0;
+  const int nk = HALF ? g.K / PBK + 1 : g.K / PBK;
   const int mine = wave < nk ? (nk - 1 - wave) / NW + 1 : 0;   // k-steps of this wavefront
   auto issue = [&](int i, int slot) {
     const int kstep = wave + i * NW;
     const long koff = (long)kstep * PBK;
     char* base = ring + slot * STAGE_BYTES;
-    const bool tail = half_last && kstep == nk - 1;
+    const bool tail = HALF && kstep == nk - 1;
 #pragma unroll
     for (int q = 0; q < LB; ++q)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcb[q] + (tail ? koff + kmajor_tail_shift(q) : koff)),
@@ -1059,7 +1319,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_split_kernel(GemmDev g, int
     const char* tb = ta + LA * 1024;
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
-      if (kk == 1 && half_last && wave + i * NW == nk - 1) break;   // no second half
+      if (kk == 1 && HALF && wave + i * NW == nk - 1) break;   // no second half
       bf16x8_t fa[MB], fb[NB];
 #pragma unroll
       for (int x = 0; x < MB; ++x) fa[x] = w48_fragment(ta, x * 16, kk);
@@ -1106,17 +1366,22 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_split_kernel(GemmDev g, int
   });
 }
 
-template <int MB, int NB, int NW, int NS>
-static bool launch_split_inst(const GemmDev& d, hipStream_t st) {
+template <int MB, int NB, int NW, int NS, bool HALF>
+static bool launch_split_half(const GemmDev& d, hipStream_t st) {
   constexpr int RING_BYTES = NW * NS * 2 * (MB + NB) * 1024, XCH_BYTES = NW * MB * NB * 1024;
   constexpr int LDS_BYTES = RING_BYTES > XCH_BYTES ? RING_BYTES : XCH_BYTES;
   static_assert(LDS_BYTES <= 160 * 1024, "rings exceed the LDS of a CU");
-  auto kern = gemm_bf16_split_kernel<MB, NB, NW, NS>;
+  auto kern = gemm_bf16_split_kernel<MB, NB, NW, NS, HALF>;
   static LdsLimitOnce lds_limit;   // per instantiation
   if (!lds_limit.ensure((const void*)kern, LDS_BYTES)) return false;
   const int tiles_m = (d.M + 16 * MB - 1) / (16 * MB), tiles_n = (d.N + 16 * NB - 1) / (16 * NB);
   hipLaunchKernelGGL(kern, dim3(((tiles_m * tiles_n + 7) / 8) * 8), dim3(64 * NW), LDS_BYTES, st, d, tiles_m, tiles_n);
   return true;
+}
+
+template <int MB, int NB, int NW, int NS>
+static bool launch_split_inst(const GemmDev& d, hipStream_t st) {
+  return d.K % PBK ? launch_split_half<MB, NB, NW, NS, true>(d, st) : launch_split_half<MB, NB, NW, NS, false>(d, st);
 }
 
 // Run time of a tiling in picoseconds: rounds over the CUs times (fixed part of a tile + rows per contraction value).
@@ -1161,17 +1426,27 @@ static bool launch_pipe_layout(const GemmDev& d, int batch, hipStream_t st) {
   return launch_pipe_inst<128, 128, 2, 4, AK, BKM, TC, 2>(d, batch, st);
 }
 
+// Run time of a tile that one CU works on at a time, in picoseconds, measured on products of whole rounds: fixed part
+// (launch, first stages, plain epilogue), time per contraction value, and 200 per output for a GeLU epilogue.
+struct RingTile { int bm, bn; long fixed_ps, k_ps; };
+static long ring_time(const GemmDev& d, const RingTile& t) {
+  const long tiles = (long)((d.M + t.bm - 1) / t.bm) * ((d.N + t.bn - 1) / t.bn);
+  const bool gelu = d.epilogue == EPI_BIAS_GELU || d.epilogue == EPI_MUL_GELU_GRAD || d.epilogue == EPI_BIAS_GELU_DERIV;
+  return (tiles + 255) / 256 * (t.fixed_ps + t.k_ps * d.K + (gelu ? 200L * t.bm * t.bn : 0));
+}
+
 bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32, int batch, hipStream_t st) {
   if (d.K % (PBK / 2) || out_f32 || batch != 1) return false;
   if (a_kmajor && b_kmajor) {
-    // Tile choice.  Every CU has to work through ceil(tiles / 256) tiles.  With work for all CUs the cost of a tiling
-    // is that count times the tile area; among equals the larger tile fetches fewer bytes per flop, then the squarer one.
-    struct Cand { int bm, bn; };
-    static const Cand cands[] = {{128, 128}, {128, 96}, {128, 144}, {128, 192}, {256, 144}, {256, 192}, {256, 256}};
+    // Tile choice among the rings.  Every CU has to work through ceil(tiles / 256) tiles.  With work for all CUs the cost
+    // of a tiling is that count times the tile area; among equals the larger tile fetches fewer bytes per flop, then the
+    // squarer one.
+    static const RingTile cands[] = {{128, 128, 4300000, 8600}, {128, 96, 4500000, 7500}, {128, 144, 6000000, 10000},
+                                     {128, 192, 4300000, 11500}, {256, 144, 8500000, 14500}, {256, 192, 10200000, 19200}};
     int best = 0;
     long best_cost = 0, best_area = 0, best_perim = 0;
-    for (int i = 0; i < 7; ++i) {
-      const Cand& c = cands[i];
+    for (int i = 0; i < 6; ++i) {
+      const RingTile& c = cands[i];
       if (i > 0 && d.N % c.bn) continue;
       const long tl = (long)((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn);
       const long area = (long)c.bm * c.bn, cost = ((tl + 255) / 256) * area, perim = c.bm + c.bn;
@@ -1185,6 +1460,21 @@ bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32,
     long split_cost = 0;
     const int split = split_tile_choice(d, &split_cost);
     if (split_cost < tiling_cost(d, cands[best].bm, cands[best].bn, 3000000)) return launch_split(d, split, st);
+    // The ping-pong kernel's tiles where their run time, estimated from the same kind of measurements, is below that of
+    // the ring's tile: outputs wide enough to fill the CUs with 256-row tiles.  It needs two k-steps, and 32-bit
+    // offsets within an operand panel.
+    static const RingTile pp[] = {{256, 128, 7500000, 12200}, {256, 192, 8000000, 17400}, {256, 256, 8000000, 21000}};
+    if (d.K > PBK && d.lda <= 1 << 20 && d.ldb <= 1 << 20 && d.K <= 1 << 20) {
+      int take = -1;
+      long least = ring_time(d, cands[best]);
+      for (int i = 0; i < 3; ++i) {
+        const long c = ring_time(d, pp[i]);
+        if (c < least) { least = c; take = i; }
+      }
+      if (take == 0) return launch_pingpong_inst<4, 2, 2, 2>(d, st);
+      if (take == 1) return launch_pingpong_inst<4, 2, 2, 3>(d, st);
+      if (take == 2) return launch_pingpong_inst<2, 4, 4, 2>(d, st);
+    }
     switch (best) {
       // one 128x96 tile per CU: 8 consumer + 8 producer waves, three stages (measured 24 us against 33 us for the
       // 4096x768x3072 product)
@@ -1192,22 +1482,8 @@ bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32,
       case 2: return launch_w48s_inst<2, 3, 3, 3, 2, 4, bf16_t>(d, st);   // 128x144: 12 + 4 waves
       case 3: return launch_w48s_inst<2, 4, 3, 3, 1, 8, bf16_t>(d, st);   // 128x192: 8 + 8 waves
       case 4: return launch_w48s_inst<4, 3, 3, 3, 1, 4, bf16_t>(d, st);   // 256x144: 12 + 4 waves
-      case 5: {
-        // 256x192: two stages only (112 KiB).  8 consumer waves with 64x96 wave tiles + 4 producers reach 975 TFLOP/s
-        // on a 3072-deep contraction (16 symmetric waves: 840), but run the epilogue on half the waves, which costs
-        // more than the loop gains on a 768-deep one whenever the epilogue does more than add a bias (GeLU forward
-        // 40 against 56 us, multiply by the saved derivative 28 against 34 us).
-        const bool heavy_epilogue = d.epilogue == EPI_BIAS_GELU || d.epilogue == EPI_MUL_GELU_GRAD ||
-                                    d.epilogue == EPI_BIAS_GELU_DERIV || d.epilogue == EPI_MUL_AUX;
-        if (heavy_epilogue && d.K <= 1536) return launch_w48_inst<4, 4, 2, 1, bf16_t>(d, st);
-        return launch_w48s_inst<4, 2, 6, 2, 1, 4, bf16_t>(d, st);
-      }
-      // 256x256 (a 4096 x 4096 output: one tile per CU instead of four 128x128 ones, half the operand bytes per
-      // flop): 16 symmetric waves with 64x64 wave tiles, two stages.  Measured on 4096 x 4096 x 1024: 35 us against
-      // 56 us (bias), 50 against 78 (GeLU + derivative); 1.2 PFLOP/s on a 4096-deep contraction.  The
-      // producer/consumer form would need 8 computing waves with 64x128 wave tiles, which do not fit the registers
-      // of three waves per SIMD (146 spilled).
-      case 6: return launch_w48_inst<4, 4, 2, 1, bf16_t, 4>(d, st);
+      // 256x192, 16 symmetric waves, two stages: single k-steps and panels beyond the ping-pong kernel's offsets
+      case 5: return launch_w48_inst<4, 4, 2, 1, bf16_t>(d, st);
       default: break;
     }
     // 128x128: the same producer/consumer kernel with 64x64 wave tiles

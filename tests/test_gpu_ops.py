@@ -158,6 +158,16 @@ def test_gemm_split_tiles_and_half_steps(M, N, K, epi):
         check(lin + R)
 
 
+# The ping-pong kernel: each of its three tiles (256x128, 256x192, 256x256 by the widths), ragged in both directions and
+# with a last group of two tile rows; two and three k-steps, which run its end without its main loop, and more, odd and
+# even, with and without half a step at the end.  Bounds as above.
+@pytest.mark.parametrize("epi", ["bias", "gelu_pair", "residual"])
+@pytest.mark.parametrize("K", [96, 128, 160, 192, 256, 352, 448])
+@pytest.mark.parametrize("N", [2016, 3040, 4064])
+def test_gemm_pingpong_tiles(N, K, epi):
+    test_gemm_split_tiles_and_half_steps(3488, N, K, epi)
+
+
 def test_gemm_gelu_epilogue_at_the_ends_of_the_range():
     """GeLU and its derivative far from zero, at infinity and at nan: rows of zeros, so that u is the bias."""
     announce("gemm-gelu-range")
