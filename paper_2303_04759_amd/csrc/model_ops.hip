@@ -399,17 +399,21 @@ struct MlmPlan {
   size_t e;
   int n_pad, vp;
   size_t r, t1, t2, t, mu, rstd, logits, dt, dt2, dt1, dr, loss_rows, partial, dt_part, scratch_bytes;
-  int dt_splits;   // the vocabulary-deep product dt = dlogits . Word is taken in this many slices of the contraction
+  int dt_splits, dt_depth;   // the vocabulary-deep product dt = dlogits . Word: slices of the contraction and their depth (the last may be shorter)
 };
 
 // dt has only n_pad/128 x hidden/128 output tiles (60 for the BERT-base head) under a contraction as deep as the
-// vocabulary: slicing the contraction fills the chip.  Largest count up to 16 that divides the 64-deep steps.
-static int dt_split_count(int vp) {
-  if (vp % 64) return 1;
+// vocabulary: slicing the contraction fills the chip.  Largest count up to 16 that divides the 64-deep steps; where none
+// does (odd multiples of 32, prime step counts), at most 16 slices of 256 or more and a shorter one in a launch of its
+// own (128 x 256 outputs over 5024: one slice 67 us on two workgroups, 15 slices and the rest 24 with their sum).
+static int dt_slice_depth(int vp) {
   const int steps = vp / 64;
-  for (int s = 16; s > 1; --s)
-    if (steps % s == 0 && steps / s >= 8) return s;
-  return 1;
+  if (vp % 64 == 0)
+    for (int s = 16; s > 1; --s)
+      if (steps % s == 0 && steps / s >= 8) return vp / s;
+  if (vp < 1024) return vp;
+  const int depth = (vp / 32 + 15) / 16 * 32;
+  return depth < 256 ? 256 : depth;
 }
 static MlmPlan mlm_plan(const raf_mlm_desc& d) {
   MlmPlan p{};
@@ -428,7 +432,8 @@ static MlmPlan mlm_plan(const raf_mlm_desc& d) {
   if (c1 > pf) pf = c1;
   if (c2 > pf) pf = c2;
   p.partial = bump256(o, pf * 4);
-  p.dt_splits = d.precision == RAF_BF16_AMP ? dt_split_count(p.vp) : 1;
+  p.dt_depth = d.precision == RAF_BF16_AMP ? dt_slice_depth(p.vp) : p.vp;
+  p.dt_splits = (p.vp + p.dt_depth - 1) / p.dt_depth;
   p.dt_part = bump256(o, p.dt_splits > 1 ? (size_t)p.dt_splits * p.n_pad * d.hidden * 4 : 0);
   p.scratch_bytes = o;
   return p;
@@ -603,14 +608,22 @@ extern "C" raf_status raf_mlm_head_fwd_bwd(const raf_mlm_desc* desc, const raf_m
   if (p.dt_splits > 1) {
     // dt = dlogits Word in slices of the contraction (float partial results), then their sum
     GemmArgs g = gemm_args_default();
-    const int kc = VP / p.dt_splits;
+    const int kc = p.dt_depth, whole = VP / kc;
     g.M = NP; g.N = H; g.K = kc;
     g.a = logits; g.lda = VP; g.a_kmajor = 1;
     g.b = w->word; g.ldb = H; g.b_kmajor = 0;
     g.c = sc + p.dt_part; g.ldc = H; g.out_f32 = 1;
-    g.batch = p.dt_splits;
+    g.batch = whole;
     g.sa[0] = kc; g.sb[0] = (long)kc * H; g.sc[0] = (long)NP * H;
     RAF_TRY(launch_gemm(prec, g, st));
+    if (whole < p.dt_splits) {   // what is left of the contraction
+      g.K = VP - whole * kc;
+      g.a = (const char*)logits + (size_t)whole * kc * p.e;
+      g.b = (const char*)w->word + (size_t)whole * kc * H * p.e;
+      g.c = sc + p.dt_part + (size_t)whole * NP * H * 4;
+      g.batch = 1;
+      RAF_TRY(launch_gemm(prec, g, st));
+    }
     const long n = (long)NP * H;
     hipLaunchKernelGGL((sum_slices_kernel<bf16_t>), dim3((n / 8 + 255) / 256), dim3(256), 0, st,
                        (const float*)(sc + p.dt_part), p.dt_splits, n, (bf16_t*)dt);
