@@ -1109,8 +1109,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_pingpong_kernel(GemmDev g, int 
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
   };
-  // the products of quadrant (x, y); the compiler waits for the fragments, whose reads were issued before the swap
-  auto products = [&](int x, int y, bool both) {
+  // The products of quadrant (x, y); the compiler waits for their fragments, whose reads were issued before the swap.  The
+  // fourth phase reads for the next k-step (`drain`), and the last k-step of a contraction with half a step leaves
+  // fragments unused: no product waits for those reads, so the phase does, before it hands its turn over.  Waiting in
+  // every phase of the others too costs up to 3 % (8192 x 8192 x 8192 699 -> 710 us), in the fourth alone nothing.
+  auto products = [&](int x, int y, bool both, bool drain) {
     swap_roles();
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -1122,6 +1125,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_pingpong_kernel(GemmDev g, int 
 #pragma unroll
         for (int j = 0; j < NH; ++j)
           acc[x][y][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[y][kk][j], fa[kk][i], acc[x][y][i][j], 0, 0, 0);
+    }
+    if (HALF || drain) {
+      __builtin_amdgcn_sched_barrier(0);
+      lds_reads_done();
     }
     __builtin_amdgcn_s_setprio(0);
     swap_roles();
@@ -1138,9 +1145,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_pingpong_kernel(GemmDev g, int 
 
   // k-step `it` of parity F.  Quadrants (0,F) (0,1-F) (1,1-F) (1,F): the last phase leaves the registers of B half 1-F
   // free for the fragments that k-step it + 1 starts with, so that no phase reads more than 2 MH fragments.  A half
-  // buffer is refilled two swaps or more after its last read was issued: all its reads have returned by then (each
-  // wave's products waited for them).  Order of a wave's requests: B[F] A[0] B[1-F] A[1] of each k-step; every wait
-  // leaves the last five (fewer at the end) in flight and is for what the next phase reads.
+  // buffer is refilled two phases after the phase that reads it.  A wave's reads have returned before the swap that closes
+  // their phase, and the other group runs half a phase apart: a barrier lies between the last return and the request.
+  // Order of a wave's requests: B[F] A[0] B[1-F] A[1] of each k-step; every wait leaves the last five (fewer at the end)
+  // in flight and is for what the next phase reads.
   auto kstep = [&](auto parity, int it, int rest) {
     constexpr int F = decltype(parity)::value;
     const bool both = !HALF || rest > 0;
@@ -1151,7 +1159,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pingpong_kernel(GemmDev g, int 
     } else {
       wait_halves(n1h, n0h);
     }
-    products(0, F, both);
+    products(0, F, both, false);
     read_b(1 - F, F);
     if (rest >= 2) {
       load_b(F, it + 2, F);
@@ -1161,7 +1169,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pingpong_kernel(GemmDev g, int 
     } else {
       wait_halves(n0h, n0h);
     }
-    products(0, 1 - F, both);
+    products(0, 1 - F, both, false);
     read_a(1, F);
     if (rest >= 2) {
       load_a(0, it + 2, F);
@@ -1169,7 +1177,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pingpong_kernel(GemmDev g, int 
     } else {
       wait_halves(n2h, n1h);
     }
-    products(1, 1 - F, both);
+    products(1, 1 - F, both, false);
     if (rest >= 1) read_b(1 - F, 1 - F);
     if (rest >= 2) {
       load_b(1 - F, it + 2, F);
@@ -1177,14 +1185,17 @@ __global__ __launch_bounds__(512) void gemm_bf16_pingpong_kernel(GemmDev g, int 
     } else {
       wait_halves(n1h, n1h);
     }
-    products(1, F, both);
+    products(1, F, both, true);
   };
   load_b(0, 0, 0); load_a(0, 0, 0); load_b(1, 0, 0); load_a(1, 0, 0);
   load_b(1, 1, 1); load_a(0, 1, 1); load_b(0, 1, 1);
   wait_halves(n2h, n3h);                        // B[0] and A[0] of k-step 0 have landed
   __builtin_amdgcn_s_barrier();
   read_b(0, 0);
-  if (wave >= 4) swap_roles();                  // the second group runs half a phase behind
+  if (wave >= 4) {                              // the second group runs half a phase behind
+    lds_reads_done();
+    swap_roles();
+  }
   __builtin_amdgcn_sched_barrier(0);
 
   int it = 0;
