@@ -1472,10 +1472,10 @@ bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32,
     const int split = split_tile_choice(d, &split_cost);
     if (split_cost < tiling_cost(d, cands[best].bm, cands[best].bn, 3000000)) return launch_split(d, split, st);
     // The ping-pong kernel's tiles where their run time, estimated from the same kind of measurements, is below that of
-    // the ring's tile: outputs wide enough to fill the CUs with 256-row tiles.  It needs two k-steps, and 32-bit
-    // offsets within an operand panel.
+    // the ring's tile: outputs wide enough to fill the CUs with 256-row tiles.  It needs two k-steps, and unsigned 32-bit
+    // offsets within an operand panel (a negative leading dimension, rows stored backwards, stays on the rings).
     static const RingTile pp[] = {{256, 128, 7500000, 12200}, {256, 192, 8000000, 17400}, {256, 256, 8000000, 21000}};
-    if (d.K > PBK && d.lda <= 1 << 20 && d.ldb <= 1 << 20 && d.K <= 1 << 20) {
+    if (d.K > PBK && d.lda >= 0 && d.ldb >= 0 && d.lda <= 1 << 20 && d.ldb <= 1 << 20 && d.K <= 1 << 20) {
       int take = -1;
       long least = ring_time(d, cands[best]);
       for (int i = 0; i < 3; ++i) {

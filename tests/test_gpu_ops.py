@@ -168,6 +168,31 @@ def test_gemm_pingpong_tiles(N, K, epi):
     test_gemm_split_tiles_and_half_steps(3488, N, K, epi)
 
 
+# Leading dimensions other than the contraction: padded rows (the ping-pong kernel sizes its buffer descriptors from them),
+# one row repeated and rows stored backwards.  Bounds as above; the padding holds nan, which no result may see.
+@pytest.mark.parametrize("M,N,K", [(3488, 4064, 192), (3488, 3040, 96), (256, 768, 800)])
+@pytest.mark.parametrize("form", ["padded", "repeated", "backwards"])
+def test_gemm_leading_dimensions(M, N, K, form):
+    announce("gemm-ld", M, N, K, form)
+    rng = np.random.default_rng(M + N + K)
+    A, W = rnd(rng, (M, K), 1), rnd(rng, (N, K), 1, 0.1)
+    lda, ldb = {"padded": (K + 40, K + 264), "repeated": (0, K), "backwards": (-K, -K)}[form]
+    if form == "padded":
+        a_dev, w_dev = (torch.full((r, ld), float("nan"), dtype=torch.bfloat16, device="cuda") for r, ld in ((M, lda), (N, ldb)))
+        a_dev[:, :K], w_dev[:, :K] = to_dev(A, torch.bfloat16), to_dev(W, torch.bfloat16)
+        a0, w0 = a_dev, w_dev
+    else:
+        a_dev, w_dev = to_dev(A, torch.bfloat16), to_dev(W, torch.bfloat16)
+        a0, w0 = (a_dev, w_dev) if form == "repeated" else (a_dev[M - 1], w_dev[N - 1])   # the calls start at row 0
+        A, W = (np.repeat(A[:1], M, axis=0), W) if form == "repeated" else (A[::-1], W[::-1])
+    c = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    raf.raf_op_gemm(1, M, N, K, a0, lda, 1, w0, ldb, 1, c, N)
+    ref = A.astype(np.float64) @ W.astype(np.float64).T
+    slack = K * 2.0 ** -24 * (np.abs(A).astype(np.float64) @ np.abs(W).astype(np.float64).T) + 1e-6
+    err = np.abs(host(c) - ref)
+    assert (err <= 2.0 ** -8 * np.abs(ref) + slack).all(), float(err.max())
+
+
 def test_gemm_gelu_epilogue_at_the_ends_of_the_range():
     """GeLU and its derivative far from zero, at infinity and at nan: rows of zeros, so that u is the bias."""
     announce("gemm-gelu-range")
