@@ -29,9 +29,11 @@ inline raf_status check_launch() {
 }
 // Raises a kernel's dynamic-LDS limit once per device.  One object per kernel instantiation (a function-local
 // static); safe from several host threads: two racing callers both set the same value.
+constexpr int LDS_LIMIT_UNRAISED = 64 * 1024;   // what every kernel may ask for as it is
 struct LdsLimitOnce {
   std::atomic<uint64_t> done{0};
   bool ensure(const void* kern, int bytes) {
+    if (bytes <= LDS_LIMIT_UNRAISED) return true;
     int dev = 0;
     const bool tracked = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64;
     const uint64_t bit = tracked ? (uint64_t)1 << dev : 0;

@@ -325,13 +325,14 @@ raf_status launch_gemm_group_wgrad(int precision, const GemmArgs* gs, int count,
     if (gs[i].a_kmajor || gs[i].b_kmajor || !gs[i].out_f32 || gs[i].batch != 1 || gs[i].epilogue != EPI_NONE)
       groupable = false;
   }
-  if (!groupable) {
+  auto one_by_one = [&]() -> raf_status {   // side work is left to the caller
     for (int i = 0; i < count; ++i) {
       raf_status rc = launch_gemm(precision, gs[i], st);
       if (rc != RAF_OK) return rc;
     }
     return RAF_OK;
-  }
+  };
+  if (!groupable) return one_by_one();
   GemmDev ds[GEMM_GROUP_MAX];
   for (int i = 0; i < count; ++i) ds[i] = to_dev(gs[i]);
   if (precision == RAF_F32) return launch_gemm_f32_group(ds, count, st) ? check_launch() : RAF_EHIP;
@@ -363,7 +364,8 @@ raf_status launch_gemm_group_wgrad(int precision, const GemmArgs* gs, int count,
       }
     }
   }
-  return launch_gemm_group_spec(ds, count, st, sd.count ? &sd : nullptr, side_taken) ? check_launch() : RAF_EHIP;
+  if (launch_gemm_group_spec(ds, count, st, sd.count ? &sd : nullptr, side_taken)) return check_launch();
+  return one_by_one();   // its LDS limit could not be raised: the register-staged kernel needs none
 }
 
 raf_status launch_gemm(int precision, const GemmArgs& g, hipStream_t st) {

@@ -323,13 +323,17 @@ static bool launch_f32_layout(const GemmDev& d, int a_kmajor, int b_kmajor, int 
   return launch_f32_inst<WGM, WGN, MB, NB, KS, NS, false, false>(d, batch, st);
 }
 
+// Where the LDS limit of the chosen tile cannot be raised, the 64x96 one runs, which needs no raised limit.
+#define RAF_F32_FALLBACK 2, 2, 2, 3, 2, 3
+static_assert(f32_lds_bytes<RAF_F32_FALLBACK>() <= LDS_LIMIT_UNRAISED, "the fallback tile needs a raised LDS limit");
+
 bool launch_gemm_f32(const GemmDev& d, int a_kmajor, int b_kmajor, int batch, hipStream_t st) {
   const F32Tile t = f32_tiles[f32_tile_choice(&d, 1, batch)];
 #define RAF_F32_CASE(BM, BN, WGM, WGN, MB, NB, KS, NS) \
-  if (t.bm == BM && t.bn == BN) return launch_f32_layout<WGM, WGN, MB, NB, KS, NS>(d, a_kmajor, b_kmajor, batch, st);
+  if (t.bm == BM && t.bn == BN && launch_f32_layout<WGM, WGN, MB, NB, KS, NS>(d, a_kmajor, b_kmajor, batch, st)) return true;
   RAF_F32_TILES(RAF_F32_CASE)
 #undef RAF_F32_CASE
-  return false;
+  return launch_f32_layout<RAF_F32_FALLBACK>(d, a_kmajor, b_kmajor, batch, st);
 }
 
 template <int WGM, int WGN, int MB, int NB, int KS, int NS>
@@ -357,10 +361,10 @@ bool launch_gemm_f32_group(const GemmDev* ds, int count, hipStream_t st) {
   if (count <= 0 || count > GEMM_GROUP_MAX) return false;
   const F32Tile t = f32_tiles[f32_tile_choice(ds, count, 1)];
 #define RAF_F32_CASE(BM, BN, WGM, WGN, MB, NB, KS, NS) \
-  if (t.bm == BM && t.bn == BN) return launch_f32_group_inst<WGM, WGN, MB, NB, KS, NS>(ds, count, st);
+  if (t.bm == BM && t.bn == BN && launch_f32_group_inst<WGM, WGN, MB, NB, KS, NS>(ds, count, st)) return true;
   RAF_F32_TILES(RAF_F32_CASE)
 #undef RAF_F32_CASE
-  return false;
+  return launch_f32_group_inst<RAF_F32_FALLBACK>(ds, count, st);
 }
 
 }  // namespace raf

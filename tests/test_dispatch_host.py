@@ -11,3 +11,22 @@ def test_negative_leading_dimensions_stay_off_the_pingpong_kernel(tmp_path):
         assert status == 0
     assert plain[1][0][0] == zero[1][0][0] == "gemm_bf16_pingpong_kernel"
     assert back_a[1][0][0] == back_b[1][0][0] == "gemm_bf16_w48s_kernel"
+
+
+def test_products_run_where_the_lds_limit_cannot_be_raised(tmp_path):
+    # as before the kernels with more than 64 KiB: no product is refused, each goes to a kernel that needs no raised limit
+    f32 = [dict(prec=0, M=M, N=N, K=96, ak=ak, bk=bk, f32=1) for M, N in ((992, 3040), (992, 2272), (992, 1504), (32, 64))
+           for ak, bk in ((1, 1), (1, 0), (0, 0), (0, 1))]
+    bf16 = [dict(prec=1, M=4096, N=3072, K=768), dict(prec=1, M=64, N=768, K=3072), dict(prec=1, M=1824, N=768, K=3072),
+            dict(prec=1, M=4096, N=3072, K=32), dict(prec=1, M=768, N=3072, K=4096, ak=0, bk=0, f32=1)]
+    cfg = dict(batch=2, seq=32, pre_ln=0, causal=0, gelu_tanh=0, precision=0, ln_eps=1e-5, dropout_p=0.1, seed=1, layer_id=0)
+    layers = [dict(cfg, hidden=64 * h, heads=h, ffn=f) for h, f in ((2, 512), (8, 2048), (8, 1504), (4, 3616))]
+    calls = [["gemm", g] for g in f32 + bf16] + [["layer_bwd", c] for c in layers]
+    raised, unraised = launches(tmp_path, calls), launches(tmp_path, calls, lds_limit_fails=True)
+    for call, (status, kernels) in zip(calls, unraised):
+        assert status == 0 and kernels, call
+    for family in ("gemm_f32_kernel", "gemm_f32_group_kernel"):   # both tiles of more than 64 KiB are among the calls
+        assert {k[1][:6] for _, ks in raised for k in ks if k[0] == family} >= {(2, 2, 2, 6, 2, 3), (2, 1, 2, 9, 4, 2)}
+    assert {k[1][:6] for _, ks in unraised for k in ks if k[0] in ("gemm_f32_kernel", "gemm_f32_group_kernel")} <= {
+        (2, 2, 2, 3, 2, 3), (2, 2, 2, 2, 2, 3), (2, 1, 2, 3, 4, 2), (1, 1, 2, 2, 8, 2)}
+    assert {k[0] for _, ks in unraised[len(f32):len(f32) + len(bf16)] for k in ks} <= {"gemm_bf16_kernel", "gemm_bf16_split_kernel"}
