@@ -208,6 +208,14 @@ static bool few_tiles(const GemmDev& d, int batch) {
   return tiles < 384;
 }
 
+// A single weight gradient of a short contraction whose 128x128 tiles find a CU each: the eight k-steps or fewer of the
+// producer/consumer kernel do not make up for its start and its 256-row tiles (0 to 8 % against it over 60 shapes of K 32
+// to 512, 576 x 768 x 128 6.5 -> 6.05 us, 4352 x 352 x 384 10.7 -> 9.9); with a second round of tiles it is the other way
+// round (5248 x 832 x 384 16.6 against 12.5, 4928 x 960 x 160 12.9 against 10.1).
+static bool short_wgrad(const GemmDev& d) {
+  return d.K <= 512 && (long)((d.M + 127) / 128) * ((d.N + 127) / 128) <= 256;
+}
+
 template <bool AK, bool BKM>
 static void launch_bf16_layout(const GemmDev& d, int out_f32, int batch, hipStream_t st) {
   if (d.M <= 64 && d.N <= 64)
@@ -376,7 +384,7 @@ raf_status launch_gemm(int precision, const GemmArgs& g, hipStream_t st) {
     if (!launch_gemm_f32(d, g.a_kmajor, g.b_kmajor, g.batch, st)) return RAF_EHIP;
   } else if (precision == RAF_BF16_AMP) {
     if (!g.a_kmajor && !g.b_kmajor && g.out_f32 && g.batch == 1 && g.epilogue == EPI_NONE && g.M >= 128 && g.N >= 128 &&
-        launch_gemm_group_spec(&d, 1, st))
+        !short_wgrad(d) && launch_gemm_group_spec(&d, 1, st))
       return check_launch();
     if (launch_gemm_pipe(d, g.a_kmajor, g.b_kmajor, g.out_f32, g.batch, st)) return check_launch();
     if (g.a_kmajor && g.b_kmajor) launch_bf16_layout<true, true>(d, g.out_f32, g.batch, st);

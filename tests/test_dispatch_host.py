@@ -30,3 +30,9 @@ def test_products_run_where_the_lds_limit_cannot_be_raised(tmp_path):
     assert {k[1][:6] for _, ks in unraised for k in ks if k[0] in ("gemm_f32_kernel", "gemm_f32_group_kernel")} <= {
         (2, 2, 2, 3, 2, 3), (2, 2, 2, 2, 2, 3), (2, 1, 2, 3, 4, 2), (1, 1, 2, 2, 8, 2)}
     assert {k[0] for _, ks in unraised[len(f32):len(f32) + len(bf16)] for k in ks} <= {"gemm_bf16_kernel", "gemm_bf16_split_kernel"}
+
+
+def test_short_single_weight_gradients_take_the_staged_kernel(tmp_path):
+    shapes = [(576, 768, 128), (4352, 352, 512), (128, 128, 32), (4352, 352, 544), (5248, 832, 384)]
+    got = launches(tmp_path, [["gemm", dict(prec=1, M=M, N=N, K=K, ak=0, bk=0, f32=1)] for M, N, K in shapes])
+    assert [(s, len(k), k[0][0]) for s, k in got] == [(0, 1, "gemm_bf16_kernel")] * 3 + [(0, 1, "gemm_bf16_spec_kernel")] * 2

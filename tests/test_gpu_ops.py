@@ -214,10 +214,12 @@ def test_gemm_gelu_epilogue_at_the_ends_of_the_range():
         assert np.array_equal(y[7:], np.zeros(N - 7)) and np.all(dy[7:] == 0.5)
 
 
-# weight-gradient form (C = A^T B, both operands row-major over the contraction, float output) at sizes that take
-# the producer/consumer kernel: full 256x128 tiles, a partial last tile in each direction, one k-step and many
+# weight-gradient form (C = A^T B, both operands row-major over the contraction, float output).  Short contractions take
+# the register-staged kernel; deep ones, and short ones of more than 256 tiles, the producer/consumer kernel: full 256x128
+# tiles, a partial last tile in each direction, half a k-step, one and many
 @pytest.mark.parametrize("M,N,K", [(256, 128, 64), (768, 768, 4096), (800, 160, 320), (2304, 768, 512),
-                                   (256, 128, 32), (288, 160, 352), (128, 128, 96)])
+                                   (256, 128, 32), (288, 160, 352), (128, 128, 96), (256, 128, 576), (288, 160, 544),
+                                   (128, 128, 1056), (5248, 832, 32), (5152, 928, 64), (5152, 928, 352)])
 def test_gemm_wgrad_form(M, N, K):
     announce("gemm-wgrad", M, N, K)
     rng = np.random.default_rng(M + 5 * N + 11 * K)
