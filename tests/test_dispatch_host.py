@@ -36,3 +36,11 @@ def test_short_single_weight_gradients_take_the_staged_kernel(tmp_path):
     shapes = [(576, 768, 128), (4352, 352, 512), (128, 128, 32), (4352, 352, 544), (5248, 832, 384)]
     got = launches(tmp_path, [["gemm", dict(prec=1, M=M, N=N, K=K, ak=0, bk=0, f32=1)] for M, N, K in shapes])
     assert [(s, len(k), k[0][0]) for s, k in got] == [(0, 1, "gemm_bf16_kernel")] * 3 + [(0, 1, "gemm_bf16_spec_kernel")] * 2
+
+
+def test_64_columns_of_a_short_contraction_take_the_three_stage_ring(tmp_path):
+    ring = [dict(prec=1, M=M, N=64, K=K, ak=0, bk=0) for M in (128, 65536) for K in (64, 128)]
+    staged = [dict(prec=1, M=160, N=64, K=64, ak=0, bk=0), dict(prec=1, M=128, N=64, K=96, ak=0, bk=0),
+              dict(prec=1, M=128, N=64, K=192, ak=0, bk=0), dict(prec=1, M=128, N=64, K=64, ak=1, bk=0)]
+    got = launches(tmp_path, [["gemm", g] for g in ring + staged])
+    assert [k[0][0] for _, k in got] == ["gemm_bf16_pipe_kernel"] * 4 + ["gemm_bf16_kernel"] * 4
