@@ -100,7 +100,7 @@ def launch_work(cfg, n_params_matrix, n_params_vector):
     return w
 
 
-KERNEL_CLASSES = (("gemm_bf16_spec_kernel", "wgrad_group"), ("gemm_bf16_group_kernel", "wgrad_group"),
+KERNEL_CLASSES = (("gemm_bf16_spec_kernel", "wgrad_group"),
                   ("gemm_f32_group", "wgrad_group"), ("gemm_bf16_", "gemm"), ("gemm_f32", "gemm"), ("attn_fwd_fused", "attn_fwd"),
                   ("attn_flash_fwd", "attn_fwd"), ("attn_bwd_full", "attn_bwd"), ("attn_flash_dq", "attn_bwd_dq"),
                   ("attn_flash_dkv", "attn_bwd_dkv"), ("ln_fwd_kernel", "ln_fwd"), ("ln_bwd_", "ln_bwd"),

@@ -87,8 +87,8 @@ __device__ __forceinline__ bf16x8_t pipe_fragment(const char* lds_tile, int row,
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, typename TC, int NS>
-__device__ __forceinline__ void pipe_body(const GemmDev& g, int tiles_m, int tiles_n, int remap, int z) {
+template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, int NS>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_kernel(GemmDev g, int tiles_m, int tiles_n) {
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -97,6 +97,7 @@ __device__ __forceinline__ void pipe_body(const GemmDev& g, int tiles_m, int til
   typedef PipeTile<BN, B_KMAJOR, NW> PB;
   constexpr int STAGE_BYTES = PA::BYTES + PB::BYTES;
   constexpr int LPS = PA::LOADS + PB::LOADS;          // loads per wave per stage
+  static_assert(NS == 2 || NS == 3, "the waits below leave at most one k-step in flight");
   extern __shared__ __attribute__((aligned(1024))) char lds[];
 
   // Tile assignment.  Consecutive workgroup ids go round-robin over the 8
@@ -105,17 +106,14 @@ __device__ __forceinline__ void pipe_body(const GemmDev& g, int tiles_m, int til
   // columns meet in one L2.
   const int ntile = tiles_m * tiles_n;
   const int per = (ntile + 7) >> 3;
-  // batched launches (many problems of a few tiles) keep the plain order: consecutive workgroups already spread
-  // over the XCDs
-  const int t = remap ? (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
   if (t >= ntile) return;
   const int m0 = (t / tiles_n) * BM, n0 = (t % tiles_n) * BN;
 
-  const int zb = z / g.nz_inner, zi = z % g.nz_inner;
-  const bf16_t* __restrict__ A = (const bf16_t*)g.a + zb * g.sa0 + zi * g.sa1;
-  const bf16_t* __restrict__ B = (const bf16_t*)g.b + zb * g.sb0 + zi * g.sb1;
-  TC* __restrict__ C = (TC*)g.c + zb * g.sc0 + zi * g.sc1;
-  bf16_t* __restrict__ AUX = g.aux ? (bf16_t*)g.aux + zb * g.sc0 + zi * g.sc1 : nullptr;
+  const bf16_t* __restrict__ A = (const bf16_t*)g.a;
+  const bf16_t* __restrict__ B = (const bf16_t*)g.b;
+  bf16_t* __restrict__ C = (bf16_t*)g.c;
+  bf16_t* __restrict__ AUX = (bf16_t*)g.aux;
 
   const int wave = threadIdx.x >> 6;
   const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
@@ -148,8 +146,7 @@ __device__ __forceinline__ void pipe_body(const GemmDev& g, int tiles_m, int til
   for (int it = 0; it < nk; ++it) {
     // loads of k-steps it+1 .. it+NS-2 may stay in flight; those of k-step `it` must have landed
     const int ahead = nk - 1 - it;
-    if (NS >= 4 && ahead >= 2) wait_vmcnt<(NS >= 4 ? 2 : 0) * LPS>();
-    else if (NS >= 3 && ahead >= 1) wait_vmcnt<(NS >= 3 ? 1 : 0) * LPS>();
+    if (NS == 3 && ahead >= 1) wait_vmcnt<LPS>();
     else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();   // stage `it` is complete for every wave; stage it-1 is free
     const int nxt = it + NS - 1;
@@ -188,26 +185,19 @@ __device__ __forceinline__ void pipe_body(const GemmDev& g, int tiles_m, int til
   }
 
   // register r of lane l holds output row (l & 31), column 8*(r/4) + 4*(l/32) + r%4 of its 32x32 block
-  epilogue_tile32<TC, TM, TN>(g, C, AUX, acc, m0 + wm, n0 + wn);
+  epilogue_tile32<bf16_t, TM, TN>(g, C, AUX, acc, m0 + wm, n0 + wn);
 }
 
-template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, typename TC, int NS>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_kernel(GemmDev g, int tiles_m, int tiles_n, int remap) {
-  pipe_body<BM, BN, WGM, WGN, A_KMAJOR, B_KMAJOR, TC, NS>(g, tiles_m, tiles_n, remap, (int)blockIdx.y);
-}
-
-template <int BM, int BN, int WGM, int WGN, bool AK, bool BKM, typename TC, int NS>
-static bool launch_pipe_inst(const GemmDev& d, int batch, hipStream_t st) {
+template <int BM, int BN, int WGM, int WGN, bool AK, bool BKM, int NS>
+static bool launch_pipe_inst(const GemmDev& d, hipStream_t st) {
   constexpr int NW = WGM * WGN;
   constexpr int LDS_BYTES = NS * (PipeTile<BM, AK, NW>::BYTES + PipeTile<BN, BKM, NW>::BYTES);
-  auto kern = gemm_bf16_pipe_kernel<BM, BN, WGM, WGN, AK, BKM, TC, NS>;
+  auto kern = gemm_bf16_pipe_kernel<BM, BN, WGM, WGN, AK, BKM, NS>;
   static LdsLimitOnce lds_limit;   // per instantiation
   if (!lds_limit.ensure((const void*)kern, LDS_BYTES)) return false;
   const int tiles_m = (d.M + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
   const int ntile = tiles_m * tiles_n;
-  const int remap = batch == 1 ? 1 : 0;
-  dim3 grid(remap ? ((ntile + 7) / 8) * 8 : ntile, batch);
-  hipLaunchKernelGGL(kern, grid, dim3(64 * NW), LDS_BYTES, st, d, tiles_m, tiles_n, remap);
+  hipLaunchKernelGGL(kern, dim3(((ntile + 7) / 8) * 8), dim3(64 * NW), LDS_BYTES, st, d, tiles_m, tiles_n);
   return true;
 }
 
@@ -623,19 +613,15 @@ __device__ __forceinline__ bf16x8_t w48_fragment(const char* lds_tile, int row0,
   return *reinterpret_cast<const bf16x8_t*>(lds_tile + r * 128 + ((c ^ ((r >> 1) & 7)) << 4));
 }
 
-// KS = 2 doubles the waves of a workgroup without adding LDS traffic: waves w and w + WGM*WGN share one 64x48
-// output block, each takes one 32-deep half of every k-step, and the halves are added through LDS at the end (each
-// wave of the pair then finishes half of the rows).  For tiles with only 4-8 waves this gives every SIMD a second
-// wave to issue MFMAs while the first waits for its LDS fragments.
+// 16 (4 x 4) symmetric wavefronts: each loads, reads and multiplies in turn.
 // HALF: the contraction ends in the middle of a k-step.  A template parameter: the test for the last step in the loops
 // costs the shapes without one 3 to 12 % (256x192 tiles, 4096 x 6144 x 2048: 116 -> 130 us).
-template <int WGM, int WGN, int NS, int KS, typename TC, int NB, bool HALF>
-__global__ __launch_bounds__(64 * WGM * WGN * KS) void gemm_bf16_w48_kernel(GemmDev g, int tiles_m, int tiles_n) {
-  constexpr int NT = WGM * WGN, NW = NT * KS, BM = 64 * WGM, BN = 16 * NB * WGN;
+template <int WGM, int WGN, int NS, bool HALF>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_w48_kernel(GemmDev g, int tiles_m, int tiles_n) {
+  constexpr int NB = 3, NW = WGM * WGN, BM = 64 * WGM, BN = 16 * NB * WGN;
   constexpr int ACH = BM / 8, BCH = BN / 8;           // KiB per operand tile
   constexpr int STAGE_BYTES = (ACH + BCH) * 1024;
   constexpr int BFIRST = ACH % NW;                    // wave that takes B chunk 0
-  static_assert(KS == 1 || KS == 2, "one or two waves per output block");
   extern __shared__ __attribute__((aligned(1024))) char lds[];
 
   const int ntile = tiles_m * tiles_n;
@@ -646,12 +632,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS) void gemm_bf16_w48_kernel(Gemm
 
   const bf16_t* __restrict__ A = (const bf16_t*)g.a;
   const bf16_t* __restrict__ B = (const bf16_t*)g.b;
-  TC* __restrict__ C = (TC*)g.c;
+  bf16_t* __restrict__ C = (bf16_t*)g.c;
   bf16_t* __restrict__ AUX = (bf16_t*)g.aux;
 
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int wt = wave % NT, kg = wave / NT;           // output block of this wave, its half of each k-step
-  const int wm = (wt / WGN) * 64, wn = (wt % WGN) * 16 * NB;
+  const int wave = threadIdx.x >> 6;
+  const int wm = (wave / WGN) * 64, wn = (wave % WGN) * 16 * NB;
 
   const bf16_t* srca[(ACH + NW - 1) / NW + 1];
   const bf16_t* srcb[(BCH + NW - 1) / NW + 1];
@@ -690,8 +675,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS) void gemm_bf16_w48_kernel(Gemm
     const char* ta = lds + stage * STAGE_BYTES;
     const char* tb = ta + ACH * 1024;
 #pragma unroll
-    for (int kh = 0; kh < 2 / KS; ++kh) {
-      const int kk = KS == 2 ? kg : kh;
+    for (int kk = 0; kk < 2; ++kk) {
       if (kk == 1 && HALF && it == nk - 1) break;   // no second half
       bf16x8_t fa[4], fb[NB];
 #pragma unroll
@@ -708,45 +692,13 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS) void gemm_bf16_w48_kernel(Gemm
     stage = stage + 1 == NS ? 0 : stage + 1;
   }
 
-  int i_begin = 0, i_end = 4;
-  // wave-private LDS for the staged epilogue: with one wave per block a slice of the ring stage that nobody reads
-  // any more (every wave has passed the last barrier, so all reads of the stage before the last one are done and no
-  // load is in flight), with wave pairs the slot this wave received its partner's accumulators in
-  // (waves whose slice does not fit that stage any more take one behind the ring: w48_stage_spill)
+  // wave-private LDS for the staged epilogue: a slice of the ring stage that nobody reads any more (every wave has passed
+  // the last barrier, so all reads of the stage before the last one are done and no load is in flight); waves whose slice
+  // does not fit that stage any more take one behind the ring (w48_stage_spill)
   constexpr int SB = epilogue_stage_bytes<NB>(), FIT = STAGE_BYTES / SB;
-  static_assert(epilogue_stage_bytes<NB>() <= 2 * NB * 64 * 16, "staging exceeds an exchange slot");
   char* stg = wave < FIT ? lds + stage * STAGE_BYTES + wave * SB : lds + NS * STAGE_BYTES + (wave - FIT) * SB;
-  if (KS == 2) {
-    // exchange: the wave with kg = 0 finishes row blocks 0-1, its partner row blocks 2-3; each sends the other half
-    __builtin_amdgcn_s_barrier();   // every wave is done with the ring
-    f32x4_t* xch = reinterpret_cast<f32x4_t*>(lds) + (wt * 2 + (kg ^ 1)) * 2 * NB * 64;   // slot read by the partner
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-      for (int j = 0; j < NB; ++j) xch[(ii * NB + j) * 64 + lane] = kg ? acc[ii][j] : acc[2 + ii][j];   // static indices: no scratch
-    __syncthreads();
-    const f32x4_t* got = reinterpret_cast<const f32x4_t*>(lds) + (wt * 2 + kg) * 2 * NB * 64;
-    stg = lds + (wt * 2 + kg) * 2 * NB * 64 * 16;
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const f32x4_t o = got[(ii * NB + j) * 64 + lane];
-        // fixed order: first k-half plus second k-half
-        if (kg == 0) acc[ii][j] = acc[ii][j] + o;
-        else acc[2 + ii][j] = o + acc[2 + ii][j];
-      }
-    i_begin = kg * 2;
-    i_end = i_begin + 2;
-  }
-
-  if constexpr (sizeof(TC) == 2) {
-    if (epilogue_can_stage(g)) {
-      epilogue_tile16_staged<NB>(g, C, AUX, acc, m0 + wm, n0 + wn, i_begin, i_end, stg);
-      return;
-    }
-  }
-  epilogue_tile16<TC, NB>(g, C, AUX, acc, m0 + wm, n0 + wn, i_begin, i_end);
+  if (epilogue_can_stage(g)) epilogue_tile16_staged<NB>(g, C, AUX, acc, m0 + wm, n0 + wn, 0, 4, stg);
+  else epilogue_tile16<bf16_t, NB>(g, C, AUX, acc, m0 + wm, n0 + wn, 0, 4);
 }
 
 // Same tiles with the waves specialised: NP producer waves only issue the direct-to-LDS loads (a wave is held for
@@ -754,6 +706,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS) void gemm_bf16_w48_kernel(Gemm
 // MFMAs), the WGM*WGN*KS consumer waves only read fragments and issue MFMAs.  One workgroup barrier per k-step keeps
 // both sides in step: after barrier `it` the consumers work on stage it while the producers refill the stage that was
 // freed and then wait until stage it+1 has landed.
+// KS = 2 doubles the waves of a workgroup without adding LDS traffic: waves w and w + WGM*WGN share one 64x48
+// output block, each takes one 32-deep half of every k-step, and the halves are added through LDS at the end (each
+// wave of the pair then finishes half of the rows).  For tiles with only 4-8 waves this gives every SIMD a second
+// wave to issue MFMAs while the first waits for its LDS fragments.
 template <int WGM, int WGN, int NB, int NS, int KS, int NP, typename TC, bool HALF>
 __global__ __launch_bounds__(64 * (WGM * WGN * KS + NP)) void gemm_bf16_w48s_kernel(GemmDev g, int tiles_m, int tiles_n) {
   constexpr int NT = WGM * WGN, NC = NT * KS, BM = 64 * WGM, BN = 16 * NB * WGN;
@@ -952,29 +908,25 @@ static bool launch_w48s_inst(const GemmDev& d, hipStream_t st) {
                    : launch_w48s_half<WGM, WGN, NB, NS, KS, NP, TC, false>(d, st);
 }
 
-template <int WGM, int WGN, int NS, int KS, typename TC, int NB, bool HALF>
+template <int WGM, int WGN, int NS, bool HALF>
 static bool launch_w48_half(const GemmDev& d, hipStream_t st) {
-  constexpr int BM = 64 * WGM, BN = 16 * NB * WGN;
-  constexpr int RING_BYTES = NS * (BM / 8 + BN / 8) * 1024 +
-                             (KS == 1 ? w48_stage_spill<NB>((BM / 8 + BN / 8) * 1024, WGM * WGN) : 0);
-  constexpr int XCH_BYTES = KS == 2 ? WGM * WGN * 2 * 2 * NB * 64 * 16 : 0;   // accumulator exchange of the wave pairs
-  constexpr int LDS_BYTES = RING_BYTES > XCH_BYTES ? RING_BYTES : XCH_BYTES;
+  constexpr int BM = 64 * WGM, BN = 48 * WGN;
+  constexpr int LDS_BYTES = NS * (BM / 8 + BN / 8) * 1024 + w48_stage_spill<3>((BM / 8 + BN / 8) * 1024, WGM * WGN);
   static_assert(LDS_BYTES <= 160 * 1024, "ring exceeds the LDS of a CU");
-  static_assert((NS - 2) * ((BM / 8 + BN / 8 + WGM * WGN * KS - 1) / (WGM * WGN * KS)) <= 24, "in-flight loads exceed wait_vmcnt_dyn");
-  auto kern = gemm_bf16_w48_kernel<WGM, WGN, NS, KS, TC, NB, HALF>;
+  static_assert((NS - 2) * ((BM / 8 + BN / 8 + WGM * WGN - 1) / (WGM * WGN)) <= 24, "in-flight loads exceed wait_vmcnt_dyn");
+  auto kern = gemm_bf16_w48_kernel<WGM, WGN, NS, HALF>;
   static LdsLimitOnce lds_limit;   // per instantiation
   if (!lds_limit.ensure((const void*)kern, LDS_BYTES)) return false;
   const int tiles_m = (d.M + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
   const int ntile = tiles_m * tiles_n;
   dim3 grid(((ntile + 7) / 8) * 8);
-  hipLaunchKernelGGL(kern, grid, dim3(64 * WGM * WGN * KS), LDS_BYTES, st, d, tiles_m, tiles_n);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * WGM * WGN), LDS_BYTES, st, d, tiles_m, tiles_n);
   return true;
 }
 
-template <int WGM, int WGN, int NS, int KS, typename TC, int NB = 3>
+template <int WGM, int WGN, int NS>
 static bool launch_w48_inst(const GemmDev& d, hipStream_t st) {
-  return d.K % PBK ? launch_w48_half<WGM, WGN, NS, KS, TC, NB, true>(d, st)
-                   : launch_w48_half<WGM, WGN, NS, KS, TC, NB, false>(d, st);
+  return d.K % PBK ? launch_w48_half<WGM, WGN, NS, true>(d, st) : launch_w48_half<WGM, WGN, NS, false>(d, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -1429,14 +1381,6 @@ static bool launch_split(const GemmDev& d, int choice, hipStream_t st) {
   }
 }
 
-// 128x128 tiles, 8 wavefronts (2 x 4), two 32 KiB stages, two workgroups per CU (16 waves): the variant for a
-// K-major A with an MN-major B (products against an untransposed row-major weight, e.g. the tied decoder of the
-// MLM head) when there are enough tiles for two workgroups per CU.
-template <bool AK, bool BKM, typename TC>
-static bool launch_pipe_layout(const GemmDev& d, int batch, hipStream_t st) {
-  return launch_pipe_inst<128, 128, 2, 4, AK, BKM, TC, 2>(d, batch, st);
-}
-
 // Run time of a tile that one CU works on at a time, in picoseconds, measured on products of whole rounds: fixed part
 // (launch, first stages, plain epilogue), time per contraction value, and 200 per output for a GeLU epilogue.
 struct RingTile { int bm, bn; long fixed_ps, k_ps; };
@@ -1494,7 +1438,7 @@ bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32,
       case 3: return launch_w48s_inst<2, 4, 3, 3, 1, 8, bf16_t>(d, st);   // 128x192: 8 + 8 waves
       case 4: return launch_w48s_inst<4, 3, 3, 3, 1, 4, bf16_t>(d, st);   // 256x144: 12 + 4 waves
       // 256x192, 16 symmetric waves, two stages: single k-steps and panels beyond the ping-pong kernel's offsets
-      case 5: return launch_w48_inst<4, 4, 2, 1, bf16_t>(d, st);
+      case 5: return launch_w48_inst<4, 4, 2>(d, st);
       default: break;
     }
     // 128x128: the same producer/consumer kernel with 64x64 wave tiles
@@ -1504,11 +1448,12 @@ bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32,
   // is issued before the first barrier (register-staged kernel: 1024 x 64 x 128 4.5 us against 4.25, 65536 x 64 x 128 9.6
   // against 8.9; with a K-major A the two are level).
   if (!a_kmajor && !b_kmajor && d.N == 64 && d.K % PBK == 0 && d.K <= 2 * PBK && d.M % 128 == 0)
-    return launch_pipe_inst<128, 64, 2, 2, false, false, bf16_t, 3>(d, batch, st);
-  // with a transposed B operand the ring only wins when there are enough tiles
-  // for two workgroups per CU; below that the register-staged kernel is faster
+    return launch_pipe_inst<128, 64, 2, 2, false, false, 3>(d, st);
+  // A K-major A with an MN-major B (products against an untransposed row-major weight, e.g. the tied decoder of the MLM
+  // head): 128x128 tiles, 8 wavefronts (2 x 4), two 32 KiB stages.  The ring only wins when there are enough tiles for
+  // two workgroups per CU; below that the register-staged kernel is faster.
   const long tiles = (long)((d.M + 127) / 128) * ((d.N + 127) / 128);
-  if (a_kmajor && !b_kmajor && d.K % PBK == 0 && d.M >= 128 && d.N >= 128 && tiles >= 384) return launch_pipe_layout<true, false, bf16_t>(d, batch, st);
+  if (a_kmajor && !b_kmajor && d.K % PBK == 0 && d.M >= 128 && d.N >= 128 && tiles >= 384) return launch_pipe_inst<128, 128, 2, 4, true, false, 2>(d, st);
   return false;
 }
 
