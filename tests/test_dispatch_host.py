@@ -1,5 +1,45 @@
 """CPU-only: which kernel a product goes to (launches.py)."""
+import pytest
+
+from gemm_shapes import F32_GROUPS, PP, SHAPES
 from launches import launches
+
+
+def layer_cfg(heads, ffn, precision=0):
+    return dict(batch=1, seq=32, hidden=64 * heads, heads=heads, ffn=ffn, pre_ln=0, causal=0, gelu_tanh=0,
+                precision=precision, ln_eps=1e-5, dropout_p=0.1, seed=1, layer_id=0)
+
+
+@pytest.mark.parametrize("epilogue", [1, 4, 5, 6])
+def test_shapes_reach_the_kernels_they_are_listed_for(tmp_path, epilogue):
+    got = launches(tmp_path, [["gemm", dict(prec=1, M=M, N=N, K=K, epi=epilogue)] for M, N, K, _, _ in SHAPES])
+    for (M, N, K, kernel, args), (status, found) in zip(SHAPES, got):
+        assert status == 0 and [f[0] for f in found] == [kernel] and found[0][1][:len(args)] == args, (M, N, K, found)
+        assert found[0][1][-1] == (1 if K % 64 else 0), (M, N, K, found)   # last argument: half a k-step at the end
+
+
+def test_every_gemm_kernel_of_the_library_is_listed(tmp_path):
+    import isa_util
+    listed = {(k, a, bool(K % 64)) for _, _, K, k, a in SHAPES}
+    for family, length in ((SHAPES[0][3], 2), ("gemm_bf16_w48s_kernel", 3), ("gemm_bf16_w48_kernel", 2), (PP, 4)):
+        built = isa_util.kernels(tmp_path, family)
+        assert len(built) == len([x for x in listed if x[0] == family]), (family, sorted(built))
+
+
+def test_float32_layers_reach_the_group_tiles_they_are_listed_for(tmp_path):
+    got = launches(tmp_path, [["layer_bwd", layer_cfg(h, f)] for h, f, _ in F32_GROUPS])
+    for (heads, ffn, tile), (status, found) in zip(F32_GROUPS, got):
+        group = [f[1] for f in found if f[0] == "gemm_f32_group_kernel"]
+        assert status == 0 and len(group) == 1, (heads, ffn, found)
+        wgm, wgn, mb, nb = group[0][:4]
+        assert (16 * wgm * mb, 16 * wgn * nb) == tile, (heads, ffn, group)
+
+
+def test_f32_shapes_of_the_value_tests_take_every_tile(tmp_path):
+    shapes = [(992, 3040), (992, 2272), (992, 1504), (992, 992), (992, 736), (32, 64)]
+    got = launches(tmp_path, [["gemm", dict(prec=0, M=M, N=N, K=96, f32=1)] for M, N in shapes])
+    tiles = [(16 * k[0][1][0] * k[0][1][2], 16 * k[0][1][1] * k[0][1][3]) for _, k in got]
+    assert tiles == [(64, 192), (64, 144), (64, 96), (64, 64), (64, 48), (32, 32)]
 
 
 def test_negative_leading_dimensions_stay_off_the_pingpong_kernel(tmp_path):
@@ -13,14 +53,18 @@ def test_negative_leading_dimensions_stay_off_the_pingpong_kernel(tmp_path):
     assert back_a[1][0][0] == back_b[1][0][0] == "gemm_bf16_w48s_kernel"
 
 
+def test_rows_far_apart_stay_on_the_ring(tmp_path):
+    got = launches(tmp_path, [["gemm", dict(prec=1, M=224, N=49152, K=K, lda=(1 << 20) + 8)] for K in (32, 96, 192)])
+    assert [k[0][0] for _, k in got] == ["gemm_bf16_w48_kernel"] * 3
+
+
 def test_products_run_where_the_lds_limit_cannot_be_raised(tmp_path):
     # as before the kernels with more than 64 KiB: no product is refused, each goes to a kernel that needs no raised limit
     f32 = [dict(prec=0, M=M, N=N, K=96, ak=ak, bk=bk, f32=1) for M, N in ((992, 3040), (992, 2272), (992, 1504), (32, 64))
            for ak, bk in ((1, 1), (1, 0), (0, 0), (0, 1))]
     bf16 = [dict(prec=1, M=4096, N=3072, K=768), dict(prec=1, M=64, N=768, K=3072), dict(prec=1, M=1824, N=768, K=3072),
             dict(prec=1, M=4096, N=3072, K=32), dict(prec=1, M=768, N=3072, K=4096, ak=0, bk=0, f32=1)]
-    cfg = dict(batch=2, seq=32, pre_ln=0, causal=0, gelu_tanh=0, precision=0, ln_eps=1e-5, dropout_p=0.1, seed=1, layer_id=0)
-    layers = [dict(cfg, hidden=64 * h, heads=h, ffn=f) for h, f in ((2, 512), (8, 2048), (8, 1504), (4, 3616))]
+    layers = [layer_cfg(h, f) for h, f in ((2, 512), (8, 2048), (8, 1504), (4, 3616))]
     calls = [["gemm", g] for g in f32 + bf16] + [["layer_bwd", c] for c in layers]
     raised, unraised = launches(tmp_path, calls), launches(tmp_path, calls, lds_limit_fails=True)
     for call, (status, kernels) in zip(calls, unraised):

@@ -11,6 +11,7 @@ from paper_2303_04759_amd.harness import DeviceLayer
 from oracle.step import train_step
 from workloads.synthetic import ADAM, CONFIGS, PARAM_NAMES, make_layer_inputs
 
+from gemm_shapes import F32_GROUPS
 from gpu_util import announce, check_update, host, rel_fro
 
 pytestmark = pytest.mark.gpu
@@ -87,6 +88,26 @@ def test_small_fp32_variants(variant):
     announce("layer small fp32", variant)
     cfg = dict(CONFIGS["tiny"], batch=3, seq=96, hidden=192, heads=3, ffn=320, ln_eps=1e-5, **variant)
     run_and_compare(cfg, seed=2, steps=2, random_affine=True, lens_override=[96, 40, 1])
+
+
+# The grouped float32 weight gradients on each of their tiles, three sequences of 32 tokens.  Per element, against the row
+# and column it comes from: a tile that misses a piece of the contraction or a block is off by the order of the element,
+# float32 sums along the step by about BWD_TOL of it.
+@pytest.mark.parametrize("heads,ffn,tile", F32_GROUPS)
+def test_weight_gradient_tiles_fp32(heads, ffn, tile):
+    announce("layer fp32 weight-gradient tiles", heads, ffn, tile)
+    cfg = dict(CONFIGS["tiny"], batch=3, seq=32, hidden=64 * heads, heads=heads, ffn=ffn, dropout_p=0.1)
+    inp = make_layer_inputs(cfg, seed=heads, random_affine=True)
+    lay = DeviceLayer(cfg, inp, ADAM)
+    lay.train_step(1)
+    p = {k: v.astype(np.float64) for k, v in inp["params"].items()}
+    z = {k: np.zeros_like(v) for k, v in p.items()}
+    ref = train_step(cfg, p, z, z, inp["x"], inp["G"], inp["seq_lens"], 1, dict(ADAM, loss_scale=cfg["loss_scale"]))
+    for k in ("w_qkv", "w_o", "w_1", "w_2"):
+        g_ref = ref["grads"][k].reshape(p[k].shape)
+        err = np.abs(host(lay.grads[k]) - g_ref)
+        rms = lambda axis: np.sqrt(np.mean(g_ref ** 2, axis=axis, keepdims=True))
+        assert (err <= BWD_TOL[0] * (np.abs(g_ref) + np.maximum(rms(0), rms(1)))).all(), (k, float(err.max()))
 
 
 def test_tiny_shape_in_bf16_amp():

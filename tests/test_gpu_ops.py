@@ -11,6 +11,7 @@ from oracle import layer as L
 from oracle.philox import dropout_keep
 from workloads.synthetic import round_to_bf16
 
+from gemm_shapes import SHAPES
 from gpu_util import announce, cdtype, host, rel_fro, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -65,9 +66,9 @@ def test_gemm_layouts(precision, ak, bk, M, N, K):
     assert rel_fro(host(c), ref) <= (1e-5 if precision == 0 else 4e-3)
 
 
-# K-major x K-major bf16 products large enough that the launcher leaves the 128x128 tile: by its cost rule these
-# shapes take the 128x96, 128x144, 128x192, 256x144, 256x192 and 256x256 tiles, with partial last row tiles and full
-# layer shapes.
+# K-major x K-major bf16 products large enough that the launcher leaves the 128x128 tile, with partial last row tiles and
+# full layer shapes: the 128x96, 128x144 and 256x144 tiles of the rings, the 256x192 ones of single k-steps and the
+# 256x192 and 256x256 ones of the ping-pong kernel.
 TILE_FAMILY_SHAPES = [(992, 2304, 128), (1984, 2304, 64), (2016, 3072, 64), (3968, 2304, 64), (3968, 3072, 64),
                       (4096, 768, 768), (4096, 2304, 768), (4096, 3072, 128), (4096, 768, 3072),
                       (4096, 4096, 1024), (3968, 4096, 64), (2016, 8192, 128)]
@@ -119,10 +120,10 @@ def test_gemm_256x256_tile_epilogues():
     assert np.max(np.abs(got - ref)) <= 0.02 * (1.0 + np.max(np.abs(ref)))
 
 
-# Few output tiles: the sizes take each tile of the split kernel (16x16, 16x32, 32x32, 32x48, 32x64, 64x32, 64x48, 64x64,
-# 64x96), with ragged last tiles, contractions shorter than the wavefronts' shares and ones that end in half a k-step;
-# then every tile of the rings with such a contraction.  Bound per element: bf16 rounding of the result (2^-9 relative,
-# twice that for the stored pre-activation path) and float32 accumulation of K products.
+# Contractions that end in half a k-step, over the tiles of the split kernel with ragged last tiles and contractions shorter
+# than the wavefronts' shares, over the rings and over the ping-pong kernel (gemm_shapes.py lists which shape reaches which
+# kernel).  Bound per element: bf16 rounding of the result (2^-9 relative, twice that for the stored pre-activation path)
+# and float32 accumulation of K products.
 @pytest.mark.parametrize("epi", ["bias", "gelu_pair", "residual"])
 @pytest.mark.parametrize("M,N,K", [(32, 32, 32), (64, 768, 800), (128, 768, 352), (256, 768, 800), (96, 3072, 96),
                                    (480, 1056, 352), (1056, 480, 352), (992, 736, 1056), (992, 1024, 1056),
@@ -168,6 +169,30 @@ def test_gemm_pingpong_tiles(N, K, epi):
     test_gemm_split_tiles_and_half_steps(3488, N, K, epi)
 
 
+# Every kernel and tile with whole and with half k-steps at the end.  Bounds as above.
+@pytest.mark.parametrize("epi", ["bias", "gelu_pair", "residual"])
+@pytest.mark.parametrize("M,N,K", [s[:3] for s in SHAPES])
+def test_gemm_every_kernel_and_tile(M, N, K, epi):
+    test_gemm_split_tiles_and_half_steps(M, N, K, epi)
+
+
+# A panel wider than the ping-pong kernel's offsets reach stays on the 256x192 ring: rows of A 2^20 + 8 values apart.
+@pytest.mark.parametrize("K", [32, 96, 192])
+def test_gemm_rows_far_apart(K):
+    announce("gemm-rows-far-apart", K)
+    M, N, ld = 224, 49152, (1 << 20) + 8
+    rng = np.random.default_rng(K)
+    A, W = rnd(rng, (M, K), 1), rnd(rng, (N, K), 1, 0.1)
+    wide = torch.empty(M, ld, dtype=torch.bfloat16, device="cuda")
+    wide[:, :K] = to_dev(A, torch.bfloat16)
+    c = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    raf.raf_op_gemm(1, M, N, K, wide, ld, 1, to_dev(W, torch.bfloat16), K, 1, c, N)
+    ref = A.astype(np.float64) @ W.astype(np.float64).T
+    slack = K * 2.0 ** -24 * (np.abs(A).astype(np.float64) @ np.abs(W).astype(np.float64).T) + 1e-6
+    err = np.abs(host(c) - ref)
+    assert (err <= 2.0 ** -8 * np.abs(ref) + slack).all(), float(err.max())
+
+
 # Leading dimensions other than the contraction: padded rows (the ping-pong kernel sizes its buffer descriptors from them),
 # one row repeated and rows stored backwards.  Bounds as above; the padding holds nan, which no result may see.
 @pytest.mark.parametrize("M,N,K", [(3488, 4064, 192), (3488, 3040, 96), (256, 768, 800)])
@@ -193,17 +218,18 @@ def test_gemm_leading_dimensions(M, N, K, form):
     assert (err <= 2.0 ** -8 * np.abs(ref) + slack).all(), float(err.max())
 
 
-def test_gemm_gelu_epilogue_at_the_ends_of_the_range():
+# The accurate forms on the split kernel, the one-exponential ones on a ring and on the ping-pong kernel.
+@pytest.mark.parametrize("M,N,K", [(64, 64, 64), (1056, 992, 192), (1184, 3392, 192)])
+def test_gemm_gelu_epilogue_at_the_ends_of_the_range(M, N, K):
     """GeLU and its derivative far from zero, at infinity and at nan: rows of zeros, so that u is the bias."""
-    announce("gemm-gelu-range")
-    M = N = K = 64
+    announce("gemm-gelu-range", M, N, K)
     bf = torch.bfloat16
     bias = torch.zeros(N)
     bias[:7] = torch.tensor([1e4, -1e4, 1e30, -1e30, float("inf"), float("nan"), 3e38])
-    a = torch.zeros(M, K, dtype=bf, device="cuda")
+    a, w = (torch.zeros(n, K, dtype=bf, device="cuda") for n in (M, N))
     for tanh in (0, 1):
         c, d = (torch.zeros(M, N, dtype=bf, device="cuda") for _ in range(2))
-        raf.raf_op_gemm(1, M, N, K, a, K, 1, a, K, 1, c, N, epilogue=raf.EPI_BIAS_GELU_DERIV, bias=bias.cuda(), aux=d,
+        raf.raf_op_gemm(1, M, N, K, a, K, 1, w, K, 1, c, N, epilogue=raf.EPI_BIAS_GELU_DERIV, bias=bias.cuda(), aux=d,
                         gelu_tanh=tanh)
         y, dy = host(c)[0], host(d)[0]
         want = bias.to(bf).double().numpy()
