@@ -338,7 +338,7 @@ raf_status raf_mlm_head_fwd_bwd(const raf_mlm_desc *desc, const raf_mlm_tensors 
 /* ---- single fused operators, exported for per-kernel parity tests and
  * per-kernel roofline measurement; the layer calls above use the same kernels. */
 
-/* C[M,N] = epilogue(alpha * A.B) on the MFMA (bf16) or FMA (f32) GEMM kernel.
+/* C[M,N] = epilogue(alpha * A.B) on the bf16 or the float32 MFMA GEMM kernels.
  * a_kmajor=1: A element (i,k) at a[i*lda+k]; 0: at a[k*lda+i].
  * b_kmajor=1: B element (k,j) at b[j*ldb+k]; 0: at b[k*ldb+j].
  * epilogue: 0 none, 1 +bias[j], 2 +bias then GeLU (pre-activation stored to

@@ -211,17 +211,19 @@ __device__ __forceinline__ float group_max(float v) {
 }
 
 // ------------------------------------------------------------------- GeLU --
-// erf by the rational approximation 7.1.28 of Abramowitz & Stegun:
-// erf(x) = 1 - (1 + a1 x + ... + a6 x^6)^-16 for x >= 0, |error| <= 3e-7;
-// branch-free and about a third of the instructions of the library erff.
-// 1/x for x >= 1: the hardware reciprocal and one Newton step, which leaves half an ulp and costs 4 instructions; the
-// IEEE division costs 11, a third of the GeLU epilogues.  The bound keeps the step finite where the result is zero anyway.
+// 1/x for 1 <= x <= 1e30: the hardware reciprocal and one Newton step in 4 instructions; the IEEE division costs 11, a
+// third of the GeLU epilogues.  Compared on the card for every float of that range: always the correctly rounded quotient.
+// The bound keeps the step finite where the result is zero anyway; for nan it gives 1e-30, and the callers' other factors
+// carry the nan on.
 __device__ __forceinline__ float rcp_from_one(float x) {
   x = fminf(x, 1e30f);
   const float r = __builtin_amdgcn_rcpf(x);
   return fmaf(fmaf(-x, r, 1.0f), r, r);
 }
 
+// erf by the rational approximation 7.1.28 of Abramowitz & Stegun:
+// erf(x) = 1 - (1 + a1 x + ... + a6 x^6)^-16 for x >= 0, |error| <= 3e-7;
+// branch-free and about a third of the instructions of the library erff.
 __device__ __forceinline__ float erf_as(float x) {
   const float ax = fabsf(x);
   float p = 0.0000430638f;
@@ -373,7 +375,8 @@ inline GemmArgs gemm_args_default() {
 raf_status launch_gemm(int precision, const GemmArgs& g, hipStream_t st);
 // up to 4 independent weight-gradient GEMMs (A, B MN-major, float out) in one launch
 // side / nside: optional column sums (ColsumJob, at most two, bf16, same row count), reds / nred: optional second
-// stages of two-stage column sums (at most three), that the launch may take along on CUs its tiles leave idle;
+// stages of two-stage column sums (at most three), that the launch may take along, on the CUs that its last round of tiles
+// leaves idle where these suffice, else on all of them after their tiles;
 // *side_taken tells whether it did (all of them or none), otherwise the caller launches them itself.
 // nonfinite: optional device flag; when the side work is taken the launch also sets it to 1 if any weight gradient
 // or any of the side sums is inf or nan (otherwise it is left alone and the caller has to check by other means)

@@ -369,8 +369,8 @@ struct ColsumSide {
 
 // Weight-gradient group (both operands MN-major, float output) on the
 // producer/consumer direct-to-LDS kernel (gemm_pipe.hip); false when a problem
-// does not fit it (K % 32, M or N not a multiple of 8) or the kernel could not be set up.  side: optional column sums; *side_taken tells whether the launch
-// computed them (it does when enough CUs are left without a tile), otherwise the caller has to.
+// does not fit it (K % 32, M or N not a multiple of 8) or its LDS limit could not be raised.  side: optional column sums;
+// *side_taken tells whether the launch computed them, otherwise the caller has to (sums wider than its workers hold).
 // side->nonfinite is honoured only when the side work is taken (*side_taken).
 bool launch_gemm_group_spec(const GemmDev* ds, int count, hipStream_t st, const ColsumSide* side = nullptr,
                             bool* side_taken = nullptr);
@@ -381,7 +381,7 @@ bool launch_gemm_group_spec(const GemmDev* ds, int count, hipStream_t st, const 
 bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32, int batch, hipStream_t st);
 
 // Full-precision products on the matrix cores (gemm_f32.hip), one problem (batched or not) of any layout, or up to
-// GEMM_GROUP_MAX of the weight-gradient layout in one launch.  False: the kernel could not be set up (raf_last_hip_error).
+// GEMM_GROUP_MAX of the weight-gradient layout in one launch.  False: nothing was launched (count out of range).
 bool launch_gemm_f32(const GemmDev& d, int a_kmajor, int b_kmajor, int batch, hipStream_t st);
 bool launch_gemm_f32_group(const GemmDev* ds, int count, hipStream_t st);
 

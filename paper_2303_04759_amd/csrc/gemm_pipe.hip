@@ -222,9 +222,12 @@ static bool launch_pipe_inst(const GemmDev& d, hipStream_t st) {
 // to 62 us, 1024-wide 126 to 108 us, 2048-wide 406 to 371 us, bit-identical.  What is
 // left: per 64 contraction values a 256x128 tile needs 1024 clocks of MFMA, about
 // 900 of LDS (131 KiB read transposed at 210 bytes/clock, 48 written) and 850 of
-// direct loads (48 KiB at 57), and takes 1900.  Fragments read across the barrier,
-// two wave groups alternating between reading and computing, 128x64 wave
-// tiles and 256x256 tiles all measured slower (66 to 70 us, 64, 141).
+// direct loads (48 KiB at 57), and takes 1900.  On the 768-wide group fragments read
+// across the barrier, two wave groups alternating between reading and computing,
+// 128x64 wave tiles and 256x256 tiles (108 of them for 256 CUs) all measured slower
+// (66 to 70 us, 64, 141), each with whole stages handed over at a barrier.  Half-tile
+// buffers as in the ping-pong kernel below, and the wider groups, whose 256x256 tiles
+// would fill the CUs, were not measured.
 //
 // LDS layout of a [64][ROWS] tile: 16-byte chunk cc of k-row k sits at chunk
 // cc ^ wg_swz(k), which spreads the eight k-rows x 32 bytes of half a fragment
@@ -935,7 +938,7 @@ static bool launch_w48_inst(const GemmDev& d, hipStream_t st) {
 // barrier swaps the roles.  A wave tile is split in 2 x 2 quadrants and a k-step in four phases (quadrant 00: reads the
 // upper half of the A fragments and the left half of the B ones, 01: the right half of B, 11: the lower half of A, 10:
 // nothing), and each half of an operand tile has a buffer of its own in each of the two stages: it is free
-// again as soon as its one phase is over, so its next filling is requested ten half-phases (about 1.2 us) before it is
+// again as soon as its one phase is over, so its next filling is requested ten half-phases (about 1.6 us) before it is
 // waited for and the ring needs no third stage.
 //
 // What bounds it: per k-step a 256x256 tile takes 2048 clocks of MFMA and the loop about 2800; 8192 x 8192 x 8192 runs at
@@ -1063,8 +1066,9 @@ __global__ __launch_bounds__(512) void gemm_bf16_pingpong_kernel(GemmDev g, int 
   };
   // The products of quadrant (x, y); the compiler waits for their fragments, whose reads were issued before the swap.  The
   // fourth phase reads for the next k-step (`drain`), and the last k-step of a contraction with half a step leaves
-  // fragments unused: no product waits for those reads, so the phase does, before it hands its turn over.  Waiting in
-  // every phase of the others too costs up to 3 % (8192 x 8192 x 8192 699 -> 710 us), in the fourth alone nothing.
+  // fragments unused: no product waits for those reads, so the phase does, before it hands its turn over.  (In every phase
+  // the wait costs 0.5 to 1 % on 8192 x 8192 x 8192, 684 against 691 us and 686 against 689 in the other order, and
+  // nothing on layer products; half steps take it, which keeps the rule free of a branch.)
   auto products = [&](int x, int y, bool both, bool drain) {
     swap_roles();
     __builtin_amdgcn_s_setprio(1);
@@ -1348,7 +1352,8 @@ static bool launch_split_inst(const GemmDev& d, hipStream_t st) {
 }
 
 // Run time of a tiling in picoseconds: rounds over the CUs times (fixed part of a tile + rows per contraction value).
-constexpr long CU_LINE_PS = 32;      // per operand row and contraction value, measured for every kernel of this file
+// Decides between the split kernel and the rings, which are both bound by the rate of new lines.
+constexpr long CU_LINE_PS = 32;      // per operand row and contraction value: split kernel and rings (ping-pong 34 to 41)
 static long tiling_cost(const GemmDev& d, int bm, int bn, long fixed_ps) {
   const long tiles = (long)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn);
   return (tiles + 255) / 256 * (fixed_ps + CU_LINE_PS * (bm + bn) * d.K);
@@ -1382,7 +1387,11 @@ static bool launch_split(const GemmDev& d, int choice, hipStream_t st) {
 }
 
 // Run time of a tile that one CU works on at a time, in picoseconds, measured on products of whole rounds: fixed part
-// (launch, first stages, plain epilogue), time per contraction value, and 200 per output for a GeLU epilogue.
+// (launch, first stages, plain epilogue), time per contraction value, and 200 per output for a GeLU epilogue.  Decides
+// between a ring and the ping-pong kernel only: tiling_cost's flat fixed part of 3 us fits the rings beside the split
+// kernel, these larger ones hold for rounds that fill the chip.  By both tables together 187 of 2418 layer products
+// (hidden 128 to 2048, 64 to 8192 rows) get a tile that another candidate would beat by 5 % or more, most of them by the
+// GeLU term, which tiling_cost lacks.
 struct RingTile { int bm, bn; long fixed_ps, k_ps; };
 static long ring_time(const GemmDev& d, const RingTile& t) {
   const long tiles = (long)((d.M + t.bm - 1) / t.bm) * ((d.N + t.bn - 1) / t.bn);
@@ -1394,8 +1403,8 @@ bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32,
   if (d.K % (PBK / 2) || out_f32 || batch != 1) return false;
   if (a_kmajor && b_kmajor) {
     // Tile choice among the rings.  Every CU has to work through ceil(tiles / 256) tiles.  With work for all CUs the cost
-    // of a tiling is that count times the tile area; among equals the larger tile fetches fewer bytes per flop, then the
-    // squarer one.
+    // of a tiling is that count times the tile area (the fixed parts below are left out of it); among equals the larger
+    // tile fetches fewer bytes per flop, then the squarer one.
     static const RingTile cands[] = {{128, 128, 4300000, 8600}, {128, 96, 4500000, 7500}, {128, 144, 6000000, 10000},
                                      {128, 192, 4300000, 11500}, {256, 144, 8500000, 14500}, {256, 192, 10200000, 19200}};
     int best = 0;

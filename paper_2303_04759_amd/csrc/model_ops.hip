@@ -403,9 +403,10 @@ struct MlmPlan {
 };
 
 // dt has only n_pad/128 x hidden/128 output tiles (60 for the BERT-base head) under a contraction as deep as the
-// vocabulary: slicing the contraction fills the chip.  Largest count up to 16 that divides the 64-deep steps; where none
-// does (odd multiples of 32, prime step counts), at most 16 slices of 256 or more and a shorter one in a launch of its
-// own (128 x 256 outputs over 5024: one slice 67 us on two workgroups, 15 slices and the rest 24 with their sum).
+// vocabulary: slicing the contraction fills the chip.  Largest count up to 16 that divides the 64-deep steps (30528: 9);
+// where none does (odd multiples of 32, prime step counts), at most 16 slices of 256 or more and a shorter one in a launch
+// of its own (128 x 256 outputs over 5024: one slice 67 us on two workgroups, 15 slices and the rest 24 with their sum).
+// Step counts of two or three times a large prime keep the 2 or 3 slices that divide them (10112: 2 of 5056).
 static int dt_slice_depth(int vp) {
   const int steps = vp / 64;
   if (vp % 64 == 0)
