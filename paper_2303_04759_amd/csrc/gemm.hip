@@ -246,6 +246,11 @@ static GemmDev to_dev(const GemmArgs& g) {
   d.M = g.M; d.N = g.N; d.K = g.K;
   d.a = g.a; d.lda = g.lda; d.b = g.b; d.ldb = g.ldb; d.c = g.c; d.ldc = g.ldc;
   d.alpha = g.alpha; d.epilogue = g.epilogue; d.bias = g.bias; d.aux = g.aux; d.ldaux = g.ldaux;
+  // Which form of GeLU a bf16 product has depends on its shape and not on the kernel that takes it: contractions of half a
+  // k-step and outputs of fewer than 128 rows or columns have the accurate one (their tiles are few or ragged, and a layer's
+  // K = hidden is never one of them), all others the one-exponential form wherever the epilogue is staged.
+  const bool gelu = g.epilogue == EPI_BIAS_GELU || g.epilogue == EPI_MUL_GELU_GRAD || g.epilogue == EPI_BIAS_GELU_DERIV;
+  d.gelu_exact = gelu && !g.gelu_tanh && (g.K % 64 || g.M < 128 || g.N < 128);
   d.gelu_tanh = g.gelu_tanh; d.nz_inner = g.nz_inner;
   d.sa0 = g.sa[0]; d.sa1 = g.sa[1]; d.sb0 = g.sb[0]; d.sb1 = g.sb[1]; d.sc0 = g.sc[0]; d.sc1 = g.sc[1];
   return d;

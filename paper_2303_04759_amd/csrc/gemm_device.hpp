@@ -16,6 +16,7 @@ struct GemmDev {
   const float* bias;
   void* aux; long ldaux;
   int gelu_tanh;
+  int gelu_exact;   // the staged epilogue, whose GeLU is the one-exponential form, must not be taken
   int nz_inner;
   long sa0, sa1, sb0, sb1, sc0, sc1;
 };
@@ -168,10 +169,10 @@ constexpr int epilogue_stage_bytes() {
   return 2 * 16 * (32 * NB + 16);
 }
 
-// True when the output (and aux) rows of a problem can be written 16 bytes at a time.
+// True when the output (and aux) rows of a problem can be written 16 bytes at a time (and its GeLU may be the fast form).
 __device__ __forceinline__ bool epilogue_can_stage(const GemmDev& g) {
   const unsigned long long p = (unsigned long long)g.c | (unsigned long long)g.aux;
-  return ((g.ldc | g.ldaux | (long)g.N) & 7) == 0 && (p & 15) == 0;
+  return !g.gelu_exact && ((g.ldc | g.ldaux | (long)g.N) & 7) == 0 && (p & 15) == 0;
 }
 
 // Same result as epilogue_tile16 for bf16 outputs, written through a wave-private LDS buffer: the accumulator

@@ -240,6 +240,34 @@ def test_gemm_gelu_epilogue_at_the_ends_of_the_range(M, N, K):
         assert np.array_equal(y[7:], np.zeros(N - 7)) and np.all(dy[7:] == 0.5)
 
 
+# Products of half a k-step and of fewer than 128 rows or columns have the accurate GeLU on every kernel: in the tails, where
+# the one-exponential form is off by up to 2.6e-5, each element within bf16 rounding and 4e-7 |u| (erf to 3e-7, halved, and
+# float32 rounding).  Rows of zeros, so that u is the bias.
+@pytest.mark.parametrize("M,N,K", [(1120, 928, 352), (1440, 2752, 352), (3968, 3072, 32), (96, 17632, 64), (64, 928, 352)])
+def test_gemm_gelu_tails_of_odd_and_narrow_products(M, N, K):
+    announce("gemm-gelu-tails", M, N, K)
+    bf = torch.bfloat16
+    a, w = (torch.zeros(n, K, dtype=bf, device="cuda") for n in (M, N))
+    u = torch.linspace(-6.0, 6.0, N)
+    u_bf = u.to(bf).double().numpy()
+    c, aux = (torch.zeros(M, N, dtype=bf, device="cuda") for _ in range(2))
+
+    def check(got, ref, at):
+        assert (np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 4e-7 * (1.0 + np.abs(at))).all(), float(np.abs(got - ref).max())
+    raf.raf_op_gemm(1, M, N, K, a, K, 1, w, K, 1, c, N, epilogue=raf.EPI_BIAS_GELU_DERIV, bias=u.cuda(), aux=aux)
+    u64 = u.double().numpy()
+    check(host(c), L.gelu(u64, False)[None, :], u64)
+    check(host(aux), L.gelu_grad(u64, False)[None, :], u64)
+    raf.raf_op_gemm(1, M, N, K, a, K, 1, w, K, 1, c, N, epilogue=raf.EPI_BIAS_GELU, bias=u.cuda(), aux=aux)
+    check(host(c), L.gelu(u_bf, False)[None, :], u_bf)
+    one = torch.zeros(M, K, dtype=bf, device="cuda")
+    one[:, 0] = 1
+    w[:, 0] = 1
+    aux.copy_(u.to(bf).cuda().expand(M, N))
+    raf.raf_op_gemm(1, M, N, K, one, K, 1, w, K, 1, c, N, epilogue=raf.EPI_MUL_GELU_GRAD, aux=aux)
+    check(host(c), L.gelu_grad(u_bf, False)[None, :], u_bf)
+
+
 # weight-gradient form (C = A^T B, both operands row-major over the contraction, float output).  Short contractions take
 # the register-staged kernel; deep ones, and short ones of more than 256 tiles, the producer/consumer kernel: full 256x128
 # tiles, a partial last tile in each direction, half a k-step, one and many
