@@ -1399,6 +1399,30 @@ static long ring_time(const GemmDev& d, const RingTile& t) {
   return (tiles + 255) / 256 * (t.fixed_ps + t.k_ps * d.K + (gelu ? 200L * t.bm * t.bn : 0));
 }
 
+static long tile_count(const GemmDev& d, int bm, int bn) { return (long)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn); }
+
+// Where the register-staged kernel, several workgroups per CU, still beats the ring or ping-pong tile `bm` x `bn`:
+// * A contraction of half a k-step in several rounds, nothing read beside the operands: its time is that of the stores, which
+//   the staged kernel's rounds overlap (39616 x 3840 x 32 113 us against 148, 4608 x 13120 x 32 51 against 57; with a second
+//   operand in the epilogue the rings win by a quarter).
+// * Outputs of fewer than 128 rows or columns that no single round of split tiles covers (`narrow`: 16384 and more on the
+//   long side), where the tile is mostly padding.  Both sides measured over 32, 64 and 96 by 16480 to 131072, K 32 to 2048:
+//   in one round the large tile wins from 64 rows on (64 x 24576 x 256 6.6 us against 8.6), with 32 on the 128-row tiles from
+//   K = 256 (32 x 36000 x 256 7.6 against 9.1) and on the 256-row ones from K = 1024; plain products, which the staged kernel
+//   stores fastest, of K <= 128 do not (64 x 20000 x 64 4.4 against 5.0).  In several rounds staged wins with 32 rows (65536
+//   x 32 x 128 8.1 against 11.5), for plain products (64 x 50272 x 512 15.4 against 17.6), with a single k-step on the
+//   small tiles (57344 x 64 x 64 7.7 against 9.6), against 256x256 tiles (64 x 131072 x 128 16.4 against 19.5) and from
+//   three rounds on (98304 x 64 x 256 14.8 against 18.5).
+static bool staged_wins(const GemmDev& d, int bm, int bn, bool narrow) {
+  const int side = d.M < d.N ? d.M : d.N;
+  const long rounds = (tile_count(d, bm, bn) + 255) / 256;
+  if (d.K < PBK && rounds >= 2 && (d.epilogue == EPI_NONE || d.epilogue == EPI_BIAS)) return true;
+  if (!narrow) return false;
+  if (side <= 32 && (rounds >= 2 || d.K < (bm < 256 ? 256 : 1024))) return true;
+  if (d.epilogue == EPI_NONE && side <= 64 && d.K <= 2 * PBK) return true;
+  return rounds >= 3 || (rounds == 2 && (d.epilogue == EPI_NONE || bm * bn == 256 * 256 || (d.K <= PBK && bm * bn <= 128 * 128)));
+}
+
 bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32, int batch, hipStream_t st) {
   if (d.K % (PBK / 2) || out_f32 || batch != 1) return false;
   if (a_kmajor && b_kmajor) {
@@ -1423,21 +1447,27 @@ bool launch_gemm_pipe(const GemmDev& d, int a_kmajor, int b_kmajor, int out_f32,
     // rings and 13.5 on 64x96 split tiles, the 3072-deep ones 26.6 and 26.1.
     long split_cost = 0;
     const int split = split_tile_choice(d, &split_cost);
-    if (split_cost < tiling_cost(d, cands[best].bm, cands[best].bn, 3000000)) return launch_split(d, split, st);
+    // (Rounds of split tiles do not overlap: outputs of fewer than 128 rows or columns take them in one round only.)
+    const bool narrow = (d.M < 128 || d.N < 128) && tile_count(d, split_tiles[split].bm, split_tiles[split].bn) > 256;
+    if (!narrow && split_cost < tiling_cost(d, cands[best].bm, cands[best].bn, 3000000)) return launch_split(d, split, st);
     // The ping-pong kernel's tiles where their run time, estimated from the same kind of measurements, is below that of
     // the ring's tile: outputs wide enough to fill the CUs with 256-row tiles.  It needs two k-steps, and unsigned 32-bit
     // offsets within an operand panel (a negative leading dimension, rows stored backwards, stays on the rings).
     static const RingTile pp[] = {{256, 128, 7500000, 12200}, {256, 192, 8000000, 17400}, {256, 256, 8000000, 21000}};
+    int take = -1;
     if (d.K > PBK && d.lda >= 0 && d.ldb >= 0 && d.lda <= 1 << 20 && d.ldb <= 1 << 20 && d.K <= 1 << 20) {
-      int take = -1;
       long least = ring_time(d, cands[best]);
       for (int i = 0; i < 3; ++i) {
         const long c = ring_time(d, pp[i]);
         if (c < least) { least = c; take = i; }
       }
+    }
+    const RingTile& chosen = take < 0 ? cands[best] : pp[take];
+    if (staged_wins(d, chosen.bm, chosen.bn, narrow)) return false;
+    if (take >= 0) {
       if (take == 0) return launch_pingpong_inst<4, 2, 2, 2>(d, st);
       if (take == 1) return launch_pingpong_inst<4, 2, 2, 3>(d, st);
-      if (take == 2) return launch_pingpong_inst<2, 4, 4, 2>(d, st);
+      return launch_pingpong_inst<2, 4, 4, 2>(d, st);
     }
     switch (best) {
       // one 128x96 tile per CU: 8 consumer + 8 producer waves, three stages (measured 24 us against 33 us for the

@@ -88,3 +88,18 @@ def test_64_columns_of_a_short_contraction_take_the_three_stage_ring(tmp_path):
               dict(prec=1, M=128, N=64, K=192, ak=0, bk=0), dict(prec=1, M=128, N=64, K=64, ak=1, bk=0)]
     got = launches(tmp_path, [["gemm", g] for g in ring + staged])
     assert [k[0][0] for _, k in got] == ["gemm_bf16_pipe_kernel"] * 4 + ["gemm_bf16_kernel"] * 4
+
+
+def test_products_of_one_wide_round_or_more_stay_on_the_staged_kernel_where_it_wins(tmp_path):
+    split, ring, pp, staged = "gemm_bf16_split_kernel", "gemm_bf16_w48s_kernel", "gemm_bf16_pingpong_kernel", "gemm_bf16_kernel"
+    want = [((32, 16384, 128, 1), split), ((16384, 32, 128, 1), split),                 # one round of split tiles
+            ((32, 16480, 128, 1), staged), ((20480, 32, 192, 1), staged), ((32, 32768, 256, 1), ring),
+            ((45056, 32, 512, 1), staged), ((36000, 32, 1024, 1), pp), ((32, 131072, 2048, 1), staged),
+            ((64, 24576, 64, 1), ring), ((64, 24576, 64, 0), staged), ((64, 24576, 192, 0), ring),
+            ((57344, 64, 64, 1), staged), ((57344, 64, 128, 1), pp), ((98304, 64, 256, 1), staged),
+            ((64, 131072, 128, 1), staged), ((64, 50272, 512, 0), staged), ((64, 50272, 512, 1), ring),
+            ((96, 65536, 32, 1), staged), ((96, 65536, 128, 4), pp),
+            ((39616, 3840, 32, 0), staged), ((39616, 3840, 32, 4), ring), ((39616, 3840, 64, 0), ring), ((2016, 1952, 32, 1), ring)]
+    got = launches(tmp_path, [["gemm", dict(prec=1, M=M, N=N, K=K, epi=e)] for (M, N, K, e), _ in want])
+    for (shape, kernel), (status, found) in zip(want, got):
+        assert status == 0 and found[0][0] == kernel, (shape, found)
