@@ -246,9 +246,9 @@ static GemmDev to_dev(const GemmArgs& g) {
   d.M = g.M; d.N = g.N; d.K = g.K;
   d.a = g.a; d.lda = g.lda; d.b = g.b; d.ldb = g.ldb; d.c = g.c; d.ldc = g.ldc;
   d.alpha = g.alpha; d.epilogue = g.epilogue; d.bias = g.bias; d.aux = g.aux; d.ldaux = g.ldaux;
-  // Which form of GeLU a bf16 product has depends on its shape and not on the kernel that takes it: contractions of half a
-  // k-step and outputs of fewer than 128 rows or columns have the accurate one (their tiles are few or ragged, and a layer's
-  // K = hidden is never one of them), all others the one-exponential form wherever the epilogue is staged.
+  // Contractions that end in half a k-step and outputs of fewer than 128 rows or columns have the accurate GeLU on every
+  // kernel: the split and register-staged kernels, which take most of them, have no other, and in the tails (u = -4: gelu is
+  // -1.3e-4) the one-exponential form of the staged epilogues is off by up to 2.6e-5.  A layer of 128 rows has neither.
   const bool gelu = g.epilogue == EPI_BIAS_GELU || g.epilogue == EPI_MUL_GELU_GRAD || g.epilogue == EPI_BIAS_GELU_DERIV;
   d.gelu_exact = gelu && !g.gelu_tanh && (g.K % 64 || g.M < 128 || g.N < 128);
   d.gelu_tanh = g.gelu_tanh; d.nz_inner = g.nz_inner;
